@@ -247,8 +247,8 @@ def run(p, w, storage, mode, steps, warmup, tune_steps, variant=None, graph_step
     blocks1 = p.local_blocks()
     bs = BYTES[storage]
     local_ps = 0.5 * (blocks0 + blocks1) * 64
-    computed = c1["cum_upd"] - c0["cum_upd"]
-    read = c1["cum_read"] - c0["cum_read"]
+    computed = c1["cum_run_upd"] - c0["cum_run_upd"]
+    read = c1["cum_run_read"] - c0["cum_run_read"]
     shear_ms, shear_n = prof["shear"]
     out = {
         "elapsed": elapsed, "steps": steps, "ms_per_step": 1e3 * elapsed / steps,
@@ -259,7 +259,7 @@ def run(p, w, storage, mode, steps, warmup, tune_steps, variant=None, graph_step
         "kernel_ms_per_step": {k: v[0] / steps for k, v in prof.items()},
         "per_shear": [{"axis": "xyz"[w.order[s]],
                        "ms": prof["shear%d" % (s + 1)][0] / max(prof["shear%d" % (s + 1)][1], 1),
-                       "algorithmic_gb": (c1["upd%d" % s] + c1["read%d" % s]) * bs / 1e9,
+                       "algorithmic_gb": (c1["run_upd%d" % s] + c1["run_read%d" % s]) * bs / 1e9,
                        "items": c1["items%d" % s]} for s in range(3)],
     }
     for s in out["per_shear"]:

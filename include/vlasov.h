@@ -116,6 +116,9 @@ typedef struct vl_step_stats {
                              ledger_mass up to FP64 rounding, and the residual held
                              outside f stays that of the last shear of each axis */
     int64_t local_blocks; /* blocks held by local cells after the step */
+    /* of the step's ghost scheme: a ghost line that a periodic partition does
+       not translate itself (vl_fill_ghosts) counts as the local line that it
+       is an image of; vl_counters has what the shears ran */
     int64_t updated_ps[3];/* phase-space cells written by each shear (sweep order) */
     int64_t read_ps[3];   /* phase-space cells read by each shear */
     int64_t items[3];     /* (pencil, block) work items of each shear */
@@ -160,6 +163,11 @@ int vl_load_values(vl_partition *p, int64_t first_block, int64_t nblocks, const 
 /* Coalesced ghost update (Section 3, Fig. 3a): every cell of the padded box
  * outside the local box receives the block list and values of its periodic
  * image.  Once per step, before a VL_COALESCED step.  Asynchronous.
+ * With gt_level 3 and at least 3 cells along each axis no copy is made: every
+ * ghost line would be given the values of the local line that it is an image
+ * of, so the step's shears run the local lines alone and read their ends
+ * through the period, and this call only checks that the ghost lists and
+ * blocks fit their capacities.
  * VL_ERR_ARG if desc.edges is set (boundary cells need their sources). */
 int vl_fill_ghosts(vl_partition *p);
 
@@ -188,8 +196,8 @@ int vl_fill_ghosts_from(vl_partition *p, vl_partition *const *nbr);
  *        the sources of the last vl_fill_ghosts_from if there was one
  *        (required when desc.edges is set), else from periodic images.
  * Both modes give the same local result bit for bit (in FP32/BF16 storage
- * for a partition that stays in one mode: a coalesced step also carries the
- * rounding residuals of the ghost lines it translates, which a per-sweep step
+ * for a partition that stays in one mode, where ghost lines are translated: a
+ * coalesced step also carries their rounding residuals, which a per-sweep step
  * does not translate).  The ghost domain is stale afterwards.  dt > 0 [s].  stats: optional host output; if non-NULL
  * the call synchronises and also reports device-side errors.
  * Errors: VL_ERR_ARG, VL_ERR_CFL (checked on the host before launch),
@@ -299,7 +307,10 @@ int vl_set_courant_override(vl_partition *p, const double *table, int32_t stride
  * 0, 1), [7] work items, [8] work rows, [9] work counter, [10] error bits,
  * [11..13] updated, [14..16] read phase-space cells, [17..19] items per shear
  * of the last step, [20] local list region in use, [21] updated and [22] read
- * phase-space cells summed over all shears since init.  Synchronises. */
+ * phase-space cells summed over all shears since init (as in vl_step_stats:
+ * of the ghost scheme); [23..25] phase-space cells that each shear of the last
+ * step itself wrote and [26..28] read (each cell once), [29] and [30] the same
+ * summed over all shears since init.  Synchronises. */
 int vl_counters(vl_partition *p, uint64_t *out, int32_t n);
 
 /* Diagnostics: kernel timing with HIP events recorded on the partition's

@@ -306,11 +306,12 @@ class Partition:
     COUNTER_NAMES = ("ring_head", "ring_tail", "ring_limit", "ghost_slots", "ghost_list",
                      "list0", "list1", "items", "rows", "work", "err", "upd0", "upd1", "upd2",
                      "read0", "read1", "read2", "items0", "items1", "items2", "cur",
-                     "cum_upd", "cum_read")
+                     "cum_upd", "cum_read", "run_upd0", "run_upd1", "run_upd2",
+                     "run_read0", "run_read1", "run_read2", "cum_run_upd", "cum_run_read")
 
     def counters(self):
         out = np.zeros(32, np.uint64)
-        _check("vl_counters", self.lib.vl_counters(self.h, _ptr(out), 23))
+        _check("vl_counters", self.lib.vl_counters(self.h, _ptr(out), len(self.COUNTER_NAMES)))
         return {k: int(v) for k, v in zip(self.COUNTER_NAMES, out)}
 
     KERNEL_CLASSES = ("ghost_fill", "planner", "shear", "prune", "moments", "shear1", "shear2", "shear3",

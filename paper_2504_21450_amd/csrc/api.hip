@@ -84,7 +84,8 @@ Layout make_layout(const vl_desc *d)
     L.cover_stride = maxnv;
     const int bs = storage_bytes(d->storage);
     size_t o = 0;
-    L.pool = o;    o = align_up(o + (size_t)(tot + 1 + NSINK) * BLK * bs);  // + zero block + sinks
+    // + zero block + sinks + the old values of periodic lines' first cells
+    L.pool = o;    o = align_up(o + (size_t)(tot + 1 + NSINK + 2 * WRAP * NSINK) * BLK * bs);
     L.ring = o;    o = align_up(o + (size_t)lcap * 4);
     L.lstart = o;  o = align_up(o + (size_t)L.N * 8);
     L.lcount = o;  o = align_up(o + (size_t)L.N * 4);
@@ -259,6 +260,20 @@ void update_box(const vl_partition *p, int mode, int s, int lo[3], int hi[3])
         }
 }
 
+// Whether the partition's steps read the periodic images of its cells in place
+// (WRAP_ON, planner): its ghost cells are its own images (no neighbours given,
+// no simulation edge) and every ghost layer is recomputed (GT level 3; fewer
+// layers leave the outer ones at their old values, which differ from their
+// images').  Lines of fewer than 3 cells meet themselves within the stencil
+// and keep the copied ghost cells, and so does a pool so large that the slots
+// for the lines' ends would reach the row flag.
+bool wraps(const vl_partition *p)
+{
+    const vl_desc &d = p->desc;
+    return !p->has_src && !d.edges && d.gt_level == H && d.n[0] >= WRAP && d.n[1] >= WRAP && d.n[2] >= WRAP &&
+           d.block_capacity + d.ghost_block_capacity + 1 + NSINK + 2 * WRAP * NSINK < (int64_t)NEWFLAG - 1;
+}
+
 // the ledger stores after one step from `r`
 void rotate(LedgerRot &r, const int order[3], bool on)
 {
@@ -281,12 +296,13 @@ void enqueue_translate(vl_partition *p, double dt, int mode, double *ledger3, hi
     const bool ledger = p->lay.lg_cap > 0;
     LedgerRot rot = p->rot;
     p->loadable = false;
-    launch_book(D, BOOK_STEP_RESET, st);
+    const int wrap = !wraps(p) ? WRAP_OFF : mode == VL_PER_SWEEP ? WRAP_FACES : WRAP_ON;
+    launch_book(D, (nxt == 0 ? BOOK_STEP_A : BOOK_STEP_B) | (wrap == WRAP_FACES ? BOOK_FACES : 0), st);
     for (int s = 0; s < 3; s++) {
         const int d = p->desc.order[s];
         int lo[3], hi[3];
         update_box(p, mode, s, lo, hi);
-        if (mode == VL_PER_SWEEP) {
+        if (mode == VL_PER_SWEEP && wrap == WRAP_OFF) {
             int flo[3], fhi[3];
             for (int e = 0; e < 3; e++) {
                 flo[e] = H;
@@ -301,7 +317,6 @@ void enqueue_translate(vl_partition *p, double dt, int mode, double *ledger3, hi
             else
                 launch_fill(D, flo, fhi, st);
         }
-        launch_book(D, BOOK_SWEEP_RESET, st);
         LedgerIO lg{};
         if (ledger) {
             lg.old = p->lgs[rot.axis[d]];
@@ -312,16 +327,15 @@ void enqueue_translate(vl_partition *p, double dt, int mode, double *ledger3, hi
         }
         {
             ProfScope ps(p, K_PLAN);
-            if (ledger) launch_zero_i32(lg.nw.kcnt, p->lay.pen_cap, st);
-            launch_plan(D, d, s, lo, hi, dt, p->cur, lg, st);
+            if (ledger && wrap == WRAP_OFF) launch_zero_i32(lg.nw.kcnt, p->lay.pen_cap, st);
+            launch_plan(D, d, s, lo, hi, dt, p->cur, lg, wrap, st);
         }
         {
             ProfScope ps(p, K_SHEAR0 + s);
-            launch_sweep(D, d, s, lo, hi, dt, s == 2, lg, st);
+            launch_sweep(D, d, s, lo, hi, dt, s == 2, lg, wrap, st);
         }
         if (ledger3) launch_ledger_sum(D, d, lo, hi, ledger3 + s, st);
     }
-    launch_book(D, nxt == 0 ? BOOK_PRUNE_RESET_A : BOOK_PRUNE_RESET_B, st);
     {
         ProfScope ps(p, K_PRUNE);
         launch_prune(D, nxt, p->desc.order[2], st);
@@ -333,6 +347,11 @@ void enqueue_fill(vl_partition *p, hipStream_t st)
 {
     const Dev &D = p->D;
     int lo[3] = {0, 0, 0}, hi[3] = {D.P[0], D.P[1], D.P[2]};
+    if (wraps(p)) {  // the steps read the images in place
+        ProfScope ps(p, K_FILL);
+        launch_ghost_count(D, st);
+        return;
+    }
     launch_book(D, BOOK_GHOST_RESET, st);
     ProfScope ps(p, K_FILL);
     if (p->has_src)  // the sources of the last vl_fill_ghosts_from
@@ -809,13 +828,11 @@ int vl_accelerate(vl_partition *p, double dt, double qm, const double *dev_field
     }
     const int nxt = 1 - p->cur;
     p->loadable = false;
-    launch_book(D, BOOK_STEP_RESET, st);
-    launch_book(D, BOOK_SWEEP_RESET, st);  // ring limit <- tail
+    launch_book(D, nxt == 0 ? BOOK_STEP_A : BOOK_STEP_B, st);
     {
         ProfScope ps(p, K_ACCEL);
         if (launch_accel(D, maps, order, p->cur, st)) return VL_ERR_ARG;
     }
-    launch_book(D, nxt == 0 ? BOOK_PRUNE_RESET_A : BOOK_PRUNE_RESET_B, st);
     {
         ProfScope ps(p, K_PRUNE);
         launch_prune(D, nxt, -1, st);
@@ -903,11 +920,13 @@ int vl_counters(vl_partition *p, uint64_t *out, int32_t n)
     Ctl ctl;
     VL_HIP(hipMemcpyAsync(&ctl, p->D.ctl, sizeof(ctl), hipMemcpyDeviceToHost, p->stream));
     VL_HIP(hipStreamSynchronize(p->stream));
-    uint64_t v[32] = {ctl.ring_head, ctl.ring_tail, ctl.ring_limit, ctl.ghost_top, ctl.ghost_list_top,
-                      ctl.list_top[0], ctl.list_top[1], ctl.n_items, ctl.row_top, ctl.work, ctl.err,
+    uint64_t v[32] = {ctl.ring_head, ctl.ring_tail, ctl.ring_limit, ctl.ghost_top + ctl.face_slots[2],
+                      ctl.ghost_list_top + ctl.face_list[2],
+                      ctl.list_top[0], ctl.list_top[1], ctl.n_items[2], ctl.row_top[2], 0, ctl.err,
                       ctl.upd_ps[0], ctl.upd_ps[1], ctl.upd_ps[2], ctl.read_ps[0], ctl.read_ps[1],
                       ctl.read_ps[2], ctl.items[0], ctl.items[1], ctl.items[2], (uint64_t)p->cur,
-                      ctl.cum_upd, ctl.cum_read};
+                      ctl.cum_upd, ctl.cum_read, ctl.run_upd[0], ctl.run_upd[1], ctl.run_upd[2],
+                      ctl.run_read[0], ctl.run_read[1], ctl.run_read[2], ctl.cum_run_upd, ctl.cum_run_read};
     for (int i = 0; i < n; i++) out[i] = v[i];
     return VL_OK;
 }
@@ -1015,7 +1034,7 @@ int vl_autotune(vl_partition *p, double dt, int32_t mode, int32_t steps_per_vari
         VL_HIP(hipStreamSynchronize(p->stream));
         for (int s = 0; s < 3; s++) {
             t[(size_t)v * 4 + s] += ms[K_SHEAR0 + s];
-            const double cells = (double)(ctl.upd_ps[s] + ctl.read_ps[s]);
+            const double cells = (double)(ctl.run_upd[s] + ctl.run_read[s]);
             r[(size_t)v * 3 + s] += ms[K_SHEAR0 + s] * 1e9 / std::max(cells, 1.0);
         }
         t[(size_t)v * 4 + 3] += ms[K_SWEEP];

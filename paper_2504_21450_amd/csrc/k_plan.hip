@@ -18,6 +18,16 @@
 //      axis's new ledger store and maps each of them to the item of the same
 //      block in the store of the previous shear along the axis (a bitmap
 //      look-up per old item), so the shear can take that line's residual.
+// In a periodic partition (template parameter WR) only the local pencils are
+// planned: a pencil's ghost cells are its own first and last cells seen through
+// the period, so their presence bits are copied from those cells' bits, no list
+// is read for them and the row holds the local cells alone; every count of the
+// ghost scheme takes the pencil times its images in the scheme's box.
+// (Ghost lines give the values of local lines again and outnumber them in a
+// small box: of the first shear's updates they are 64 % on 16x16x8 cells, 14 %
+// on 64x64x32.  A step with moments, copied ghost lines -> local lines alone:
+// 243 -> 155 us on 8^3 dense FP64 cells, 4.71 -> 2.80 ms on 16x16x8 and 42.0 ->
+// 37.2 ms on 64x64x32 sparse FP64, 12.1 -> 9.7 ms on a 24x24x12 BF16 mixture.)
 // Each cell belongs to exactly one pencil of a shear, so the workgroup owns the
 // lists it grows.  Block ids of a chunk of the union are processed at a time
 // so the LDS footprint is bounded.
@@ -36,6 +46,7 @@ struct PlanParams {
     int R;               // chunk capacity (block ids per chunk)
     int cur;             // local list region in use
     int kstride;         // pencil key of (t1, t2): t1 + kstride t2
+    int faces;           // count the refresh of the ghost faces along d
     double dt;
     LedgerIO lg;
 };
@@ -97,6 +108,22 @@ __device__ inline long long block_sum_ll(long long v, long long *s_w)
     return r;
 }
 
+// three consecutive bits of a mask row (LDS) from bit `pos`, and the same or-ed in
+__device__ inline uint32_t row_bits3(const uint32_t *row, int pos)
+{
+    const int w = pos >> 5, s = pos & 31;
+    uint32_t v = row[w] >> s;
+    if (s > 29) v |= row[w + 1] << (32 - s);
+    return v & 7u;
+}
+__device__ inline void row_or3(uint32_t *row, int pos, uint32_t v)
+{
+    const int w = pos >> 5, s = pos & 31;
+    row[w] |= v << s;
+    if (s > 29) row[w + 1] |= v >> (32 - s);
+}
+
+template <bool WR>
 __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -131,9 +158,18 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     // before w (at most 224), or 255 for a block no updated cell holds
     uint8_t *s_cum = (uint8_t *)q; q += (size_t)R * WL;
 
-    const int p = blockIdx.x;
-    const int t1 = pp.lo1 + p % pp.n1;
-    const int t2 = pp.lo2 + p / pp.n1;
+    // WR: the grid holds the local pencils; p is the pencil's place in the
+    // scheme's box and mult its images there
+    const int m1 = WR ? D.n[pp.e1] : pp.n1;
+    const int t1 = (WR ? H : pp.lo1) + blockIdx.x % m1;
+    const int t2 = (WR ? H : pp.lo2) + blockIdx.x / m1;
+    const int p = WR ? (t1 - pp.lo1) + pp.n1 * (t2 - pp.lo2) : (int)blockIdx.x;
+    const unsigned long long mult =
+        WR ? (unsigned long long)images(t1, D.n[pp.e1], pp.lo1, pp.lo1 + pp.n1) *
+                 images(t2, D.n[pp.e2], pp.lo2, pp.lo2 + pp.n2)
+           : 1ull;
+    // the cells whose lists the pencil reads
+    const int i0 = WR ? H : 0, i1 = WR ? L - H : L;
     int co[3];
     co[pp.e1] = t1;
     co[pp.e2] = t2;
@@ -146,13 +182,21 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     // 0. cell metadata
     for (int i = tid; i < L; i += PNT) {
         const int64_t c = base + sd * i;
-        s_cs[i] = D.lstart[c];
-        s_cnt[i] = D.lcount[c];
-        s_cap[i] = D.lcapa[c];
         s_new[i] = 0;
         s_req[i] = 0;
         s_pos[i] = 0;
-        s_srt[i] = D.lsorted[c];
+        if (WR && (i < i0 || i >= i1)) {
+            s_cs[i] = 0;
+            s_cnt[i] = 0;
+            s_cap[i] = 0;
+            s_srt[i] = 0;
+            s_cc[i] = 0;
+        } else {
+            s_cs[i] = D.lstart[c];
+            s_cnt[i] = D.lcount[c];
+            s_cap[i] = D.lcapa[c];
+            s_srt[i] = D.lsorted[c];
+        }
     }
     for (int w = tid; w < W; w += PNT) s_bm[w] = 0u;
     if (tid == 0) s_base[3] = failed(D) ? 1ull : 0ull;
@@ -176,12 +220,12 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     };
     {
         int32_t nxt[4] = {-1, -1, -1, -1};
-        if (wave < L) load_ids(wave, lane, nxt);
-        for (int i = wave; i < L; i += PNW) {
+        if (i0 + wave < i1) load_ids(i0 + wave, lane, nxt);
+        for (int i = i0 + wave; i < i1; i += PNW) {
             int32_t ids[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) ids[k] = nxt[k];
-            if (i + PNW < L) load_ids(i + PNW, lane, nxt);
+            if (i + PNW < i1) load_ids(i + PNW, lane, nxt);
             file_ids(ids);
             for (int e0 = lane + 256; e0 < s_cnt[i]; e0 += 256) {  // lists longer than 256
                 load_ids(i, e0, ids);
@@ -196,8 +240,9 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     const int U = block_scan_excl(s_rank, W, s_tmp);
     // the pencil's items: item first + r for the block of union rank r
     if (tid == 0) {
-        const unsigned long long ib = U > 0 ? atomicAdd(&D.ctl->n_items, (unsigned long long)U) : 0ull;
-        if ((int64_t)(ib + U) > D.item_cap) atomicOr(&D.ctl->err, (unsigned long long)E_ITEMS);
+        const unsigned long long ib = U > 0 ? atomicAdd(&D.ctl->n_run[pp.sidx], (unsigned long long)U) : 0ull;
+        const unsigned long long vi = U > 0 ? atomicAdd(&D.ctl->n_items[pp.sidx], mult * U) : 0ull;
+        if ((int64_t)(vi + mult * U) > D.item_cap) atomicOr(&D.ctl->err, (unsigned long long)E_ITEMS);
         s_ibp = (long long)ib;
         if (p < D.pen_cap) {
             D.pen_first[p] = (int64_t)ib;
@@ -207,10 +252,42 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             if ((int64_t)(ib + U) > pp.lg.cap) {
                 atomicOr(&D.ctl->err, (unsigned long long)E_ITEMS);
             } else {
-                const int key = t1 + pp.kstride * t2;
-                pp.lg.nw.kfirst[key] = (int32_t)ib;
-                pp.lg.nw.kcnt[key] = U;
+                // WR: the images of the pencil in the scheme's box have its
+                // items' residuals, those beyond the box none
+                if (!WR) {
+                    const int key = t1 + pp.kstride * t2;
+                    pp.lg.nw.kfirst[key] = (int32_t)ib;
+                    pp.lg.nw.kcnt[key] = U;
+                } else {
+                    const int n1 = D.n[pp.e1], n2 = D.n[pp.e2];
+                    for (int k2 = t2 % n2; k2 < D.P[pp.e2]; k2 += n2)
+                        for (int k1 = t1 % n1; k1 < D.P[pp.e1]; k1 += n1) {
+                            const bool in = k1 >= pp.lo1 && k1 < pp.lo1 + pp.n1 && k2 >= pp.lo2 && k2 < pp.lo2 + pp.n2;
+                            const int key = k1 + pp.kstride * k2;
+                            pp.lg.nw.kfirst[key] = (int32_t)ib;
+                            pp.lg.nw.kcnt[key] = in ? U : 0;
+                        }
+                }
             }
+        }
+    }
+    if (WR && pp.faces && tid < 64) {  // the ghost faces along d that the scheme would refresh
+        unsigned long long slots = 0, list = 0;
+        for (int i = i0 + tid; i < i1; i += 64) {
+            const unsigned long long m = images(i, i1 - i0, 0, L) - 1;
+            slots += m * (unsigned long long)s_cnt[i];
+            list += m * (unsigned long long)(s_cnt[i] + s_cnt[i] / 4 + 32);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            slots += __shfl_xor(slots, o);
+            list += __shfl_xor(list, o);
+        }
+        if (tid == 0) {
+            const unsigned long long a = atomicAdd(&D.ctl->face_slots[pp.sidx], slots) + slots;
+            const unsigned long long b = atomicAdd(&D.ctl->face_list[pp.sidx], list) + list;
+            const unsigned long long err = ((int64_t)a > D.gcap ? (unsigned long long)E_GHOST_SLOTS : 0ull) |
+                                           ((int64_t)b > D.reg_cap[2] ? (unsigned long long)E_GHOST_LIST : 0ull);
+            if (err) atomicOr(&D.ctl->err, err);
         }
     }
     __syncthreads();
@@ -228,7 +305,13 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
         um[w] = m;
     }
 
-    long long st_upd = 0, st_read = 0, st_items = 0;
+    // the cells of a row's word w before bit b
+    auto row_below = [](int w, int b) -> uint32_t {
+        const uint32_t m = (1u << b) - 1u;
+        return WR && w == 0 ? m & ~7u : m;
+    };
+
+    long long st_upd = 0, st_read = 0, st_items = 0, st_own = 0;  // st_own: read of the line's own cells
 
     for (int r0 = 0; r0 < U; r0 += R) {
         const int rn = min(R, U - r0);
@@ -252,8 +335,8 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             tail0 = (srt + lane < cnt) ? lst[srt + lane] : -1;
         };
         int32_t nid[4] = {-1, -1, -1, -1}, ntail = -1;
-        if (wave < L) load_run(wave, nid, ntail);
-        for (int i = wave; i < L; i += PNW) {
+        if (i0 + wave < i1) load_run(i0 + wave, nid, ntail);
+        for (int i = i0 + wave; i < i1; i += PNW) {
             const int cnt = s_cnt[i], srt = s_srt[i];
             const int32_t *lst = D.lid + s_cs[i];
             const uint32_t cbit = 1u << (i & 31);
@@ -262,7 +345,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
 #pragma unroll
             for (int u = 0; u < 4; u++) ids[u] = nid[u];
             const int32_t tail0 = ntail;
-            if (i + PNW < L) load_run(i + PNW, nid, ntail);
+            if (i + PNW < i1) load_run(i + PNW, nid, ntail);
             // 256 entries are loaded at once (the run usually continues) and
             // taken 64 at a time until the first one beyond the chunk
             int pos = s_pos[i];
@@ -321,6 +404,12 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
         // growth and per-block counts
         for (int k = tid; k < rn; k += PNT) {
             uint32_t P[MAXWL], G[MAXWL];
+            if constexpr (WR) {  // the ghost cells hold what their images hold
+                uint32_t *row = s_pres + k * WL;
+                const uint32_t first = row_bits3(row, H), lst = row_bits3(row, L - 2 * H);
+                row_or3(row, 0, lst);
+                row_or3(row, L - H, first);
+            }
 #pragma unroll
             for (int w = 0; w < MAXWL; w++) P[w] = (w < WL) ? s_pres[k * WL + w] : 0u;
             const int dirs = block_dirs(D, pp.d, s_id[k], pp.dt);
@@ -331,7 +420,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 if (dirs & 2) g |= (P[w] >> 1) | (w + 1 < MAXWL ? (P[w + 1] << 31) : 0u);
                 G[w] = g & ~P[w] & um[w];
             }
-            int rowlen = 0, nnew = 0, upd = 0, rd = 0;
+            int rowlen = 0, nnew = 0, upd = 0, rd = 0, own = 0;
             bool active = false;
 #pragma unroll
             for (int w = 0; w < MAXWL; w++) {
@@ -344,6 +433,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                     nnew += popc(G[w]);
                     upd += popc(pn & um[w]);
                     rd += popc(P[w]);
+                    own += popc(P[w] & (WR ? um[w] : ~0u));
                 }
             }
             if (nnew > 0) {
@@ -365,13 +455,15 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 for (int w = 0; w < MAXWL; w++) {
                     if (w < WL) {
                         s_cum[k * WL + w] = active ? (uint8_t)run : (uint8_t)255;
-                        run += popc(P[w] | G[w]);
+                        // (WR: rows hold no left ghosts; the right ones' places stay unused)
+                        run += popc((P[w] | G[w]) & (WR && w == 0 ? ~7u : ~0u));
                     }
                 }
             }
             if (active) {
                 st_upd += upd;
                 st_read += rd;
+                st_own += own;
                 st_items += 1;
             }
         }
@@ -388,6 +480,11 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             if (have + req <= s_cap[i]) continue;
             const int ncap = (have + req) + (have + req) / 4 + 32;  // the slack of a fresh list
             const int reg = local_pencil ? pp.cur : 2;
+            if (WR && mult > 1) {  // the images' lists in the ghost region
+                const unsigned long long g = (mult - 1) * (unsigned long long)ncap;
+                if ((int64_t)(atomicAdd(&D.ctl->ghost_list_top, g) + g) > D.reg_cap[2])
+                    atomicOr(&D.ctl->err, (unsigned long long)E_LIST);
+            }
             unsigned long long *top = local_pencil ? &D.ctl->list_top[pp.cur] : &D.ctl->ghost_list_top;
             const unsigned long long nb0 = atomicAdd(top, (unsigned long long)ncap);
             if ((int64_t)(nb0 + ncap) > D.reg_cap[reg]) {
@@ -421,10 +518,11 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             s_ro[rn] = nrow;
             s_np[rn] = nnew;
             unsigned long long err = 0;
-            unsigned long long rb = atomicAdd(&D.ctl->row_top, (unsigned long long)nrow);
+            // (WR: the images' rows are counted; only the pencil's are written)
+            unsigned long long rb = atomicAdd(&D.ctl->row_top[pp.sidx], mult * (unsigned long long)nrow);
             unsigned long long nb = 0;
             unsigned long long ok = 1;
-            if ((int64_t)(rb + nrow) > D.row_cap) {
+            if ((int64_t)(rb + mult * nrow) > D.row_cap) {
                 err |= E_ROWS;
                 ok = 0;
             }
@@ -434,6 +532,10 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                     if (nb + nnew > D.ctl->ring_limit) {
                         err |= E_RING;
                         ok |= 2;  // allocation failed: new blocks go to the scratch slot
+                    }
+                    if (WR && mult > 1) {  // the images' new blocks among the ghost slots
+                        const unsigned long long g = (mult - 1) * (unsigned long long)nnew;
+                        if ((int64_t)(atomicAdd(&D.ctl->ghost_top, g) + g) > D.gcap) err |= E_GHOST_SLOTS;
                     }
                 } else {
                     nb = atomicAdd(&D.ctl->ghost_top, (unsigned long long)nnew);
@@ -498,7 +600,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                     }
                     qn++;
                     if (rows_ok) {
-                        const int pos = s_cum[k * WL + w] + popc(s_pres[k * WL + w] & ((1u << bit) - 1u));
+                        const int pos = s_cum[k * WL + w] + popc(s_pres[k * WL + w] & row_below(w, bit));
                         D.rows[rowoff + pos] = (int32_t)((uint32_t)slot | NEWFLAG);
                     }
                 }
@@ -566,12 +668,12 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 tsl0 = has ? D.lslot[te] : 0;
             };
             int32_t nids[4] = {-1, -1, -1, -1}, nsls[4] = {0, 0, 0, 0}, ntid = -1, ntsl = 0;
-            if (wave < L) load_rows(wave, nids, nsls, ntid, ntsl);
-            for (int i = wave; i < L; i += PNW) {
+            if (i0 + wave < i1) load_rows(i0 + wave, nids, nsls, ntid, ntsl);
+            for (int i = i0 + wave; i < i1; i += PNW) {
                 const int64_t at0 = s_cs[i] + s_pos[i];
                 const int n = s_cc[i];
                 const int iw = i >> 5;
-                const uint32_t below = (1u << (i & 31)) - 1u;
+                const uint32_t below = row_below(iw, i & 31);
                 int32_t ids[4], sls[4];
 #pragma unroll
                 for (int k = 0; k < 4; k++) {
@@ -579,7 +681,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                     sls[k] = nsls[k];
                 }
                 const int32_t tid0 = ntid, tsl0 = ntsl;
-                if (i + PNW < L) load_rows(i + PNW, nids, nsls, ntid, ntsl);
+                if (i + PNW < i1) load_rows(i + PNW, nids, nsls, ntid, ntsl);
                 for (int e0 = lane; e0 < n; e0 += 256) {
                     if (e0 != lane) {  // lists with more than 256 entries in the chunk
 #pragma unroll
@@ -661,12 +763,17 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     const long long u = block_sum_ll(st_upd, s_ll);
     const long long r = block_sum_ll(st_read, s_ll);
     const long long n = block_sum_ll(st_items, s_ll);
+    const long long o = block_sum_ll(st_own, s_ll);
     if (tid == 0 && n > 0) {
-        atomicAdd(&D.ctl->upd_ps[pp.sidx], (unsigned long long)(u * BLK));
-        atomicAdd(&D.ctl->read_ps[pp.sidx], (unsigned long long)(r * BLK));
-        atomicAdd(&D.ctl->items[pp.sidx], (unsigned long long)n);
-        atomicAdd(&D.ctl->cum_upd, (unsigned long long)(u * BLK));
-        atomicAdd(&D.ctl->cum_read, (unsigned long long)(r * BLK));
+        atomicAdd(&D.ctl->upd_ps[pp.sidx], mult * (unsigned long long)(u * BLK));
+        atomicAdd(&D.ctl->read_ps[pp.sidx], mult * (unsigned long long)(r * BLK));
+        atomicAdd(&D.ctl->items[pp.sidx], mult * (unsigned long long)n);
+        atomicAdd(&D.ctl->run_upd[pp.sidx], (unsigned long long)(u * BLK));
+        atomicAdd(&D.ctl->run_read[pp.sidx], (unsigned long long)(o * BLK));
+        atomicAdd(&D.ctl->cum_upd, mult * (unsigned long long)(u * BLK));
+        atomicAdd(&D.ctl->cum_read, mult * (unsigned long long)(r * BLK));
+        atomicAdd(&D.ctl->cum_run_upd, (unsigned long long)(u * BLK));
+        atomicAdd(&D.ctl->cum_run_read, (unsigned long long)(o * BLK));
     }
 }
 
@@ -692,9 +799,10 @@ void launch_zero_i32(int32_t *p, int64_t n, hipStream_t st)
 }
 
 void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, int cur,
-                 const LedgerIO &lg, hipStream_t st)
+                 const LedgerIO &lg, int wrap, hipStream_t st)
 {
     PlanParams pp;
+    pp.faces = wrap == WRAP_FACES;
     pp.cur = cur;
     pp.lg = lg;
     pp.d = d;
@@ -719,9 +827,14 @@ void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3]
     if (R < 64) R = 64;
     pp.R = R;
     size_t lds = plan_lds_bytes(D.W, R, pp.WL, pp.L);
+    if (wrap != WRAP_OFF) {
+        const int64_t np = (int64_t)D.n[pp.e1] * D.n[pp.e2];
+        hipLaunchKernelGGL(k_plan<true>, dim3((unsigned)np), dim3(PNT), lds, st, D, pp);
+        return;
+    }
     int64_t np = (int64_t)pp.n1 * pp.n2;
     if (np <= 0) return;
-    hipLaunchKernelGGL(k_plan, dim3((unsigned)np), dim3(PNT), lds, st, D, pp);
+    hipLaunchKernelGGL(k_plan<false>, dim3((unsigned)np), dim3(PNT), lds, st, D, pp);
 }
 
 }  // namespace vl

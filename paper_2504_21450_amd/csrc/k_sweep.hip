@@ -30,6 +30,8 @@
 //            accumulating.  The line's stored mass changes only by its final
 //            carry minus its starting one, which the item leaves for the FP64
 //            mass ledger.
+#include <algorithm>
+
 #include "vl_internal.h"
 #include "vl_storage.h"
 
@@ -37,7 +39,8 @@ namespace vl {
 
 struct SweepParams {
     int d, sidx, L, WL;
-    int e1, e2, lo1, n1, lo2;  // pencil geometry (to tell local pencils)
+    int wrap;                // 0, or the period: the line's cells [H, H + wrap) are its own
+                             // neighbours, seen again before and after them
     double dt;
     double sparse_min;
     const double *lg_old;    // residuals of the last shear along d, per old item
@@ -54,6 +57,43 @@ __device__ inline void wave_sync_lds()
 }
 
 constexpr uint32_t ABSENT = 0xffffffffu;
+
+// the wavefront's place-th block for the old values of a periodic line's
+// first cells (the grid holds at most NSINK wavefronts)
+__device__ __forceinline__ uint32_t wrap_slot(const Dev &D, int place)
+{
+    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    return (uint32_t)D.trash + 1 + NSINK + wave * (2 * WRAP) + (uint32_t)place;
+}
+
+// The ghost cells of a periodic line in its slot table (the local cells' are
+// in place): those before the line are its last cells, read where they lie,
+// for the march has read them before it writes its first cell; those after
+// the line are its first cells, which the march has overwritten by then, so
+// their old values are copied aside first (three blocks, which stay in the
+// cache; place: 0 or WRAP).  A block created in this shear is not held by the
+// images yet.  The copies' latency, once per item, costs less than a test in
+// each of the line's iterations would.
+template <int ST>
+__device__ __forceinline__ void wrap_slots(const Dev &D, uint32_t *srow, int L, int n, int lane, int place)
+{
+    const uint32_t lane_off = (uint32_t)lane * Storage<ST>::BYTES;
+    uint32_t sl[WRAP];
+    typename Storage<ST>::T v[WRAP];
+#pragma unroll
+    for (int k = 0; k < WRAP; k++) sl[k] = __builtin_amdgcn_readfirstlane(srow[H + k]);
+    const uint32_t last = srow[n + (lane < WRAP ? lane : 0)];
+#pragma unroll
+    for (int k = 0; k < WRAP; k++)
+        if (!(sl[k] & NEWFLAG)) v[k] = block_load_raw<ST>(block_rsrc<ST>(D.pool, sl[k]), lane_off);
+    if (lane < WRAP) srow[lane] = (last & NEWFLAG) ? ABSENT : last;
+#pragma unroll
+    for (int k = 0; k < WRAP; k++) {
+        const uint32_t to = wrap_slot(D, place + k);
+        if (!(sl[k] & NEWFLAG)) block_store(block_rsrc<ST>(D.pool, to), lane_off, v[k]);
+        if (lane == k) srow[L - WRAP + k] = (sl[k] & NEWFLAG) ? ABSENT : to;
+    }
+}
 constexpr int PF = 8;  // cells prefetched ahead of the reconstruction front
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -486,7 +526,7 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
     const int lane = threadIdx.x & 63;
     const int wv = threadIdx.x >> 6;
     const int d = sp.d, L = sp.L, WL = sp.WL;
-    const int64_t nitems = min((int64_t)D.ctl->n_items, D.item_cap);
+    const int64_t nitems = min((int64_t)D.ctl->n_run[sp.sidx], D.item_cap);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     uint32_t *srow = s_slot[wv];
     uint32_t *sseg = s_seg[wv];
@@ -526,15 +566,18 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
                 for (int k = 1; k < 6; k++) r &= (a0 >> k) | (a1 << (32 - k));
                 gap[w] = r & ((m[w] << 1) | (w > 0 ? m[w - 1] >> 31 : 0u));
             }
+            // the cells whose slots are in the row (a periodic line's own)
+            const int c0 = sp.wrap ? H : 0, c1 = sp.wrap ? H + sp.wrap : L;
+            const int left = sp.wrap ? __popc(m[0] & 7u) : 0;
             const int half = li >> 5, b = li & 31;
 #pragma unroll
             for (int w = 0; w < MAXWL; w += 2) {
                 if (w < wl) {
                     const uint32_t mw = half ? m[w + 1] : m[w];
-                    const int base = half ? pre[w + 1] : pre[w];
+                    const int base = (half ? pre[w + 1] : pre[w]) - left;
                     const int t = 32 * (w + half) + b;
                     if (t < L) {
-                        const bool pr = (mw >> b) & 1u;
+                        const bool pr = ((mw >> b) & 1u) && t >= c0 && t < c1;
                         const int rk = base + __popc(mw & ((1u << b) - 1u));
                         srow[t] = pr ? (uint32_t)D.rows[item.rowoff + rk] : ABSENT;
                     }
@@ -543,6 +586,10 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
             for (int t = L + li; t < L + 40; t += 64) srow[t] = ABSENT;
         }
         wave_sync_lds();
+        if (sp.wrap) {
+            wrap_slots<ST>(D, srow, L, sp.wrap, li, 0);
+            wave_sync_lds();
+        }
 
         // the block's coordinate along d (the mesh extents passed through an
         // empty asm, so the divisions' reciprocals are formed per item, not
@@ -597,9 +644,11 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
 // ---------------------------------------------------------------------------
 // streamed items (style 2)
 // ---------------------------------------------------------------------------
-// Build the per-cell slot table of item `it` into srow[0 .. L+40).
-__device__ __forceinline__ void build_slots(const Dev &D, int64_t it, int64_t nitems, int L, int WL, int lane,
-                                            uint32_t *srow)
+// Build the per-cell slot table of item `it` into srow[0 .. L+40) (wrap: see
+// SweepParams; place: the wavefront's blocks for this table).
+template <int ST>
+__device__ __forceinline__ void build_slots(const Dev &D, int64_t it, int64_t nitems, int L, int WL, int wrap,
+                                            int place, int lane, uint32_t *srow)
 {
     if (it >= nitems) {
         for (int t = lane; t < L + 40; t += 64) srow[t] = ABSENT;
@@ -614,21 +663,27 @@ __device__ __forceinline__ void build_slots(const Dev &D, int64_t it, int64_t ni
         m[w] = (w < WL) ? D.masks[it * D.wlmax + w] : 0u;
         pre[w + 1] = pre[w] + __popc(m[w]);
     }
+    const int c0 = wrap ? H : 0, c1 = wrap ? H + wrap : L;
+    const int left = wrap ? __popc(m[0] & 7u) : 0;
     const int half = lane >> 5, b = lane & 31;
 #pragma unroll
     for (int w = 0; w < MAXWL; w += 2) {
         if (w < WL) {
             const uint32_t mw = half ? m[w + 1] : m[w];
-            const int base = half ? pre[w + 1] : pre[w];
+            const int base = (half ? pre[w + 1] : pre[w]) - left;
             const int t = 32 * (w + half) + b;
             if (t < L) {
-                const bool pr = (mw >> b) & 1u;
+                const bool pr = ((mw >> b) & 1u) && t >= c0 && t < c1;
                 const int rk = base + __popc(mw & ((1u << b) - 1u));
                 srow[t] = pr ? (uint32_t)D.rows[item.rowoff + rk] : ABSENT;
             }
         }
     }
     for (int t = L + lane; t < L + 40; t += 64) srow[t] = ABSENT;
+    if (wrap) {
+        wave_sync_lds();
+        wrap_slots<ST>(D, srow, L, wrap, lane, place);
+    }
 }
 
 // One item of the stream: cells of X; q holds X's first 8 values on entry and
@@ -728,13 +783,14 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
     const int wv = threadIdx.x >> 6;
     const int d = sp.d, L = sp.L, WL = sp.WL;
     const int ld = (d == 0) ? (lane & 3) : (d == 1) ? ((lane >> 2) & 3) : (lane >> 4);
-    const int64_t nitems = min((int64_t)D.ctl->n_items, D.item_cap);
+    const int64_t nitems = min((int64_t)D.ctl->n_run[sp.sidx], D.item_cap);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     int64_t it = (int64_t)blockIdx.x * 4 + wv;
     if (it >= nitems) return;
     uint32_t *X = s_tab[wv][0], *Y = s_tab[wv][1];
     uint8_t *sflag = s_flg[wv];
-    build_slots(D, it, nitems, L, WL, lane, X);
+    int place = 0;  // X's blocks for the old values of the line's first cells; Y has the others
+    build_slots<ST>(D, it, nitems, L, WL, sp.wrap, place, lane, X);
     wave_sync_lds();
     const uint32_t zslot = (uint32_t)D.trash;
     constexpr int BS = Storage<ST>::BYTES;
@@ -760,7 +816,7 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
         double start_sum;
         double carry = take_residual<ST>(sp, it, start_sum);
         auto build = [&]() {
-            build_slots(D, nit, nitems, L, WL, lane, Y);
+            build_slots<ST>(D, nit, nitems, L, WL, sp.wrap, WRAP - place, lane, Y);
             wave_sync_lds();
         };
         if (npos == ~0ull)
@@ -778,6 +834,7 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
         uint32_t *tmp = X;
         X = Y;
         Y = tmp;
+        place = WRAP - place;
     }
 }
 
@@ -815,7 +872,8 @@ static dim3 persistent_grid(K kernel)
     }
     int per = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, 256, 0) != hipSuccess || per < 1) per = 1;
-    return dim3((unsigned)(per * ncu));
+    // (each wavefront has blocks of its own in the pool: NSINK in all)
+    return dim3((unsigned)std::min(per * ncu, NSINK / 4));
 }
 
 template <int ST, bool LAST, int V>
@@ -852,9 +910,10 @@ static void launch_st(const Dev &D, const SweepParams &sp, int v, hipStream_t st
 int sweep_variants() { return NVARIANTS; }
 
 void launch_sweep(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, bool last,
-                  const LedgerIO &lg, hipStream_t st)
+                  const LedgerIO &lg, int wrap, hipStream_t st)
 {
     SweepParams sp;
+    sp.wrap = wrap == WRAP_OFF ? 0 : D.n[d];
     sp.lg_old = lg.old.res;
     sp.lg_new = lg.nw.res;
     sp.lg_src = lg.src;
@@ -863,11 +922,6 @@ void launch_sweep(const Dev &D, int d, int sidx, const int lo[3], const int hi[3
     sp.sidx = sidx;
     sp.L = D.P[d];
     sp.WL = (sp.L + 31) / 32;
-    sp.e1 = (d == 0) ? 1 : 0;
-    sp.e2 = (d == 2) ? 1 : 2;
-    sp.lo1 = lo[sp.e1];
-    sp.n1 = hi[sp.e1] - lo[sp.e1];
-    sp.lo2 = lo[sp.e2];
     sp.dt = dt;
     sp.sparse_min = D.sparse_min;
     const int v = (D.sweep_variant[sidx] >= 0 && D.sweep_variant[sidx] < NVARIANTS) ? D.sweep_variant[sidx] : 0;

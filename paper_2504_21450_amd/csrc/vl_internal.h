@@ -2,13 +2,15 @@
 // the C-ABI host code of libvlasov.so.  Not part of the public ABI.
 //
 // Device layout (all inside the caller's workspace):
-//   pool    : (lcap + gcap + 1 + NSINK) blocks x 64 values of the storage type.
+//   pool    : (lcap + gcap + 1 + NSINK + 2 WRAP NSINK) blocks x 64 values of the storage type.
 //             Slots [0, lcap) belong to local cells, [lcap, lcap+gcap) to ghost
 //             cells; slot lcap+gcap is an all-zero block (what the shears read
 //             for a cell without the block; also handed out, with the error flag
 //             set, when an allocation fails) and the NSINK slots after it are
 //             write-only sinks for the shears' discarded stores, one per
-//             resident wavefront so the stores spread over the memory channels.
+//             resident wavefront so the stores spread over the memory channels;
+//             the 2 x WRAP x NSINK slots after them hold the old values of the
+//             first cells of a periodic line while a shear updates it in place.
 //   ring    : lcap int32 free local slots, a FIFO addressed by 64-bit counters
 //             (head = next to hand out, tail = next free position).
 //   cells   : per padded cell (x fastest) list start / count / capacity.
@@ -44,6 +46,7 @@ constexpr int MAXWL = MAXL / 32;       // presence-mask words per item
 constexpr int NB_MAX = 131072;         // block ids per velocity mesh
 constexpr int WAVE = 64;
 constexpr int NSINK = 8192;            // sink blocks (>= resident wavefronts)
+constexpr int WRAP = 3;                // cells a periodic line reads beyond its end (= H)
 
 // device error bits (Ctl::err)
 enum : unsigned long long {
@@ -55,9 +58,20 @@ struct Ctl {
     unsigned long long ring_head, ring_tail, ring_limit;
     unsigned long long ghost_top, ghost_list_top;
     unsigned long long list_top[2];
-    unsigned long long n_items, row_top, work;
+    // per shear of the step: items and rows of the ghost scheme, and the items
+    // the shear runs (fewer where ghost lines are images of local ones)
+    unsigned long long n_items[3], row_top[3], n_run[3];
+    // per shear: ghost slots and list entries of a face refresh that is not
+    // carried out (per-sweep steps of a periodic partition)
+    unsigned long long face_slots[3], face_list[3];
+    // ghost update that is not carried out: sums over the workgroups so far
+    unsigned long long acc_slots, acc_list, acc_ticket;
+    // phase-space cells per shear: of the ghost scheme, and those the shear
+    // itself writes and reads
     unsigned long long upd_ps[3], read_ps[3], items[3];
+    unsigned long long run_upd[3], run_read[3];
     unsigned long long cum_upd, cum_read;  // never reset: totals since init
+    unsigned long long cum_run_upd, cum_run_read;
     // error bits on a cache line of their own: every kernel reads them at its
     // start (fail-stop) while the counters above take atomics
     alignas(128) unsigned long long err;
@@ -147,6 +161,10 @@ __device__ inline int block_coord(const Dev &D, int d, int32_t b)
     return b / (D.nblk[0] * D.nblk[1]);
 }
 
+// padded positions lo <= t + k n < hi (k any integer): the periodic images of
+// position t within a range that holds it, itself included
+__host__ __device__ inline int images(int t, int n, int lo, int hi) { return (hi - 1 - t) / n + (t - lo) / n + 1; }
+
 // bit 0: some velocity cell of the block moves towards +d; bit 1: towards -d
 __device__ inline int block_dirs(const Dev &D, int d, int32_t b, double dt)
 {
@@ -201,11 +219,21 @@ void launch_fill(const Dev &D, const int lo[3], const int hi[3], hipStream_t st)
 void launch_fill_from(const Dev &D, const SrcTable &src, hipStream_t st);
 void launch_fill_box(const Dev &D, const SrcTable &src, const int lo[3], const int hi[3], hipStream_t st);
 SrcPart self_source(const Dev &D);
+// A periodic partition's ghost cells are images of its local cells, so a step
+// whose shears recompute every ghost layer that later shears read gives each
+// ghost line exactly the values of its local image.  wrap: plan and run the
+// local lines alone, their ends reading the line's own cells through the
+// period; the scheme's counts (updated cells, items, ghost slots and lists)
+// are kept by multiplying each line by its images in the scheme's box
+// [lo, hi).  faces: the scheme refreshes the ghost faces along d before this
+// shear (per-sweep mode), counted as well.
+enum { WRAP_OFF = 0, WRAP_ON = 1, WRAP_FACES = 2 };
+void launch_ghost_count(const Dev &D, hipStream_t st);
 void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, int cur,
-                 const LedgerIO &lg, hipStream_t st);
+                 const LedgerIO &lg, int wrap, hipStream_t st);
 int sweep_variants();
 void launch_sweep(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, bool last,
-                  const LedgerIO &lg, hipStream_t st);
+                  const LedgerIO &lg, int wrap, hipStream_t st);
 // n int32 zeros at p (a kernel, so that graph captures hold no memset node)
 void launch_zero_i32(int32_t *p, int64_t n, hipStream_t st);
 // FP64 sum of the terminal residuals of the shear's local pencils into *out:
@@ -253,10 +281,12 @@ void launch_gather(const Dev &D, const int32_t *slots, int64_t n, double *out, h
 // book-keeping operations (launch_book)
 enum {
     BOOK_GHOST_RESET = 1,     // ghost slot and ghost list allocators to zero
-    BOOK_SWEEP_RESET = 2,     // work list counters to zero, ring limit <- tail
-    BOOK_PRUNE_RESET_A = 3,   // ring limit <- tail, local list region A allocator to zero
-    BOOK_PRUNE_RESET_B = 4,   // same for region B
-    BOOK_STEP_RESET = 5,      // per-step statistics counters to zero
+    // start of a step: statistics and work list counters to zero, ring limit
+    // <- tail (only the pruning at the step's end moves the tail), the
+    // allocator of the list region that the pruning fills to zero
+    BOOK_STEP_A = 2,          // the pruning fills region A
+    BOOK_STEP_B = 3,          // region B
+    BOOK_FACES = 4,           // flag: ghost allocators to zero as well
 };
 
 }  // namespace vl
