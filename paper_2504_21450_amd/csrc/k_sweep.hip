@@ -62,7 +62,8 @@ constexpr uint32_t ABSENT = 0xffffffffu;
 // first cells (the grid holds at most NSINK wavefronts)
 __device__ __forceinline__ uint32_t wrap_slot(const Dev &D, int place)
 {
-    const uint32_t wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    // (visibly uniform, so the blocks' resources are formed in scalar registers)
+    const uint32_t wave = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     return (uint32_t)D.trash + 1 + NSINK + wave * (2 * WRAP) + (uint32_t)place;
 }
 
@@ -95,6 +96,13 @@ __device__ __forceinline__ void wrap_slots(const Dev &D, uint32_t *srow, int L, 
     }
 }
 constexpr int PF = 8;  // cells prefetched ahead of the reconstruction front
+// A march's slot window: 64 cells from WIN0 before the front, moved on every
+// WSTEP cells (so it holds the cells up to 64 - WIN0 - WSTEP ahead)
+constexpr int WIN0 = 4, WSTEP = 32;
+// slot table of a line: WIN0 cells before it, NM * 64 for it, and what the
+// windows, the prefetches and the unconditional march's groups read beyond it
+template <int NM>
+constexpr int TABLE = WIN0 + 64 * NM + 72;
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
@@ -113,22 +121,25 @@ __device__ __forceinline__ double uniform_f64(double v)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// The starting carry of each velocity cell of item `it`'s line: 1/64 of the
-// residual the last shear along the axis left for the same line and block (0
-// if the block was not on the line then).  The 64 equal shares add up to the
-// residual exactly; it is returned in `sum` (uniform, in scalar registers).
+// a read-only array (or one whose element is read before this kernel writes
+// it) read at a wave-uniform place through the scalar cache
+template <typename T>
+__device__ __forceinline__ T scalar_load(const T *p, int64_t i)
+{
+    return ((const __attribute__((address_space(4))) T *)(uintptr_t)p)[i];
+}
+
+// The residual that the last shear along the axis left for the line and block
+// of an item, given the old ledger item (src < 0: the block was not on the
+// line then).  Each velocity cell's carry starts from 1/64 of it; the 64 equal
+// shares add up to the residual exactly.
 template <int ST>
-__device__ __forceinline__ double take_residual(const SweepParams &sp, int64_t it, double &sum)
+__device__ __forceinline__ double take_residual(const SweepParams &sp, int32_t src)
 {
     double r = 0.0;
-    if constexpr (ST != VL_F64) {
-        if (it < sp.lg_cap) {
-            const int32_t s = (int32_t)uniform_u32((uint32_t)sp.lg_src[it]);
-            if (s >= 0) r = uniform_f64(sp.lg_old[s]);
-        }
-    }
-    sum = uniform_f64(r);  // kept in scalar registers for the whole item
-    return sum * (1.0 / BLK);
+    if constexpr (ST != VL_F64)
+        if (src >= 0) r = scalar_load(sp.lg_old, src);
+    return r;
 }
 
 // Leave the line's final carry, summed over the lanes in a fixed order, for
@@ -174,6 +185,20 @@ __device__ __forceinline__ C limited_slope(C dl, C dr, C cen)
         const C s2 = copysign((C)2.0, cen);
         const C m = fmax((C)0, fmin(fmin(fabs(cen), s2 * dl), s2 * dr));
         return copysign(m, cen);
+    }
+}
+
+// twice the limited slope, from the one-sided differences and the full
+// difference d2 = a+ - a- (so no halving is needed: scaling by two is exact)
+template <typename C>
+__device__ __forceinline__ C limited_slope2(C dl, C dr, C d2)
+{
+    if constexpr (std::is_same<C, float>::value) {
+        return __builtin_amdgcn_fmed3f(d2, __builtin_amdgcn_fmed3f(4.0f * dl, 4.0f * dr, 0.0f), 0.0f);
+    } else {
+        const C s4 = copysign((C)4.0, d2);
+        const C m = fmax((C)0, fmin(fmin(fabs(d2), s4 * dl), s4 * dr));
+        return copysign(m, d2);
     }
 }
 
@@ -346,15 +371,19 @@ __device__ __forceinline__ void march_unc(const Dev &D, const uint32_t *srow, ui
 }
 
 
-// Variant "conditional stores": the slot of each cell is read from LDS when
-// it is fetched (prefetch distance PFV) and kept in scalar registers until
-// the cell is written PFV + 3 iterations later; the store is skipped (scalar
-// branch) for cells without the block and outside the updated range.
+// Variant "conditional stores": 64 cells' slots at a time lie one per lane in
+// a window register (reread from the LDS table every 32 cells), a cell's slot
+// is broadcast from its lane when the cell is fetched (prefetch distance PFV)
+// and kept in scalar registers until the cell is written PFV + 3 iterations
+// later.  A cell without the block, or with one created this shear, is read
+// through a resource of no records: the hardware returns zero and moves
+// nothing.  The window's cells to be written are one scalar mask, so a store
+// costs one bit test (scalar branch).
 template <int ST, int DIR, bool LAST, int PFV>
 __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, uint8_t *sflag, int L, double c,
                                            int lane, double smin, double &carry, int tb, int te)
 {
-    static_assert(PFV >= 3, "the written cell's slot comes from the previous group");
+    static_assert(PFV >= 3 && PFV <= 16, "the written cell's slot comes from the previous group; window of 64 cells");
     using C = typename std::conditional<ST == VL_F64, double, float>::type;  // reconstruction type
     const bool pos = (DIR > 0) ? true : (DIR < 0) ? false : (c > 0.0);
     const double s = fabs(c);
@@ -362,12 +391,10 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
     const double Q = pos ? c * c * (1.0 - c) : s * (1.0 - s) * (1.0 - s);
     constexpr int BS = Storage<ST>::BYTES;
     const uint32_t lane_off = (uint32_t)lane * BS;
-    const uint32_t zslot = (uint32_t)D.trash;
 
-    // a cell's value from its raw slot (wave-uniform): absent or created this
-    // shear reads the all-zero block
+    // a cell's value from its raw slot (wave-uniform); flagged slots: zero
     auto fetch_raw = [&](uint32_t sl) -> C {
-        return block_load<ST>(block_rsrc<ST>(D.pool, (sl & NEWFLAG) ? zslot : sl), lane_off);
+        return block_load<ST>(block_rsrc_if<ST>(D.pool, sl, (int32_t)sl >= 0), lane_off);
     };
 
     C a1 = 0, a2 = 0;
@@ -380,38 +407,39 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
     // the prologue), of the three cells before them, and of the cells this
     // group fetches
     uint32_t prv[PFV], bef[3], cur[PFV];
+    // lane j of the window holds cell w0 - WIN0 + j
+    uint32_t win = srow[tb - WIN0 + lane];
 #pragma unroll
     for (int u = 0; u < PFV; u++) {
-        prv[u] = uniform_u32(srow[tb + u]);
+        prv[u] = (uint32_t)__builtin_amdgcn_readlane((int)win, WIN0 + u);
         q[u] = fetch_raw(prv[u]);
     }
 #pragma unroll
-    for (int i = 0; i < 3; i++) bef[i] = (tb - 3 + i >= 0) ? uniform_u32(srow[tb - 3 + i]) : ABSENT;
-    // the slot-table entry of the next iteration's fetch, read from LDS one
-    // iteration ahead so its latency is hidden behind a cell's arithmetic
-    // (the table is padded with ABSENT past L)
-    uint32_t f_next = srow[tb + PFV];
-    for (int t0 = tb; t0 < te; t0 += PFV) {
+    for (int i = 0; i < 3; i++) bef[i] = (uint32_t)__builtin_amdgcn_readlane((int)win, WIN0 - 3 + i);
+    for (int w0 = tb; w0 < te; w0 += WSTEP) {
+        if (w0 != tb) win = srow[w0 - WIN0 + lane];
+        // the window's cells that this march writes: local ones before te - 3
+        // (those from there on belong to the next segment's march)
+        const int jlo = max(0, H + WIN0 - w0), jhi = min(L - H, te - 3) + WIN0 - w0;
+        unsigned long long wm = __ballot(win != ABSENT && lane >= jlo && lane < jhi) >> (WIN0 - 3);
+        const int iend = min(WSTEP, te - w0);
+        for (int i0 = 0; i0 < iend; i0 += PFV) {
 #pragma unroll
-        for (int u = 0; u < PFV; u++) {
-            const int t = t0 + u;
-            cur[u] = uniform_u32(f_next);
-            f_next = srow[t + PFV + 1];
-            const C a = q[u];
-            q[u] = fetch_raw(cur[u]);
-            const C dl = a1 - a2, dr = a - a1;
-            const C cen = (C)0.5 * (a - a2);
-            const C da = limited_slope(dl, dr, cen);
-            const C face = a2 + (C)0.5 * (a1 - a2) - (da - da_prev) * (C)(1.0 / 6.0);
-            const C ai = a2;
-            const C dL = ai - face_prev, dR = face - ai;
-            const double dLp = (double)limited_offset(dL, dR), dRp = (double)limited_offset(dR, dL);
-            const double aid = (double)ai;
-            const double Fc = fma(P, dRp, fma(Q, dLp, c * aid));
-            const double Ff = (DIR > 0) ? Fc_prev : (DIR < 0) ? Fc : (pos ? Fc_prev : Fc);
-            if (t >= 6 && t < L && t < te) {  // past te: the next segment's march
-                const uint32_t sl3 = (u >= 3) ? prv[u - 3] : bef[u];  // cell t - 3
-                if (sl3 != ABSENT) {
+            for (int u = 0; u < PFV; u++) {
+                cur[u] = (uint32_t)__builtin_amdgcn_readlane((int)win, i0 + u + PFV + WIN0);
+                const C a = q[u];
+                q[u] = fetch_raw(cur[u]);
+                const C dl = a1 - a2, dr = a - a1;
+                const C da = limited_slope2(dl, dr, a - a2);
+                const C face = a2 + (C)0.5 * (a1 - a2) - (da - da_prev) * (C)(0.5 / 6.0);
+                const C ai = a2;
+                const C dL = ai - face_prev, dR = face - ai;
+                const double dLp = (double)limited_offset(dL, dR), dRp = (double)limited_offset(dR, dL);
+                const double aid = (double)ai;
+                const double Fc = fma(P, dRp, fma(Q, dLp, c * aid));
+                const double Ff = (DIR > 0) ? Fc_prev : (DIR < 0) ? Fc : (pos ? Fc_prev : Fc);
+                if ((wm >> u) & 1ull) {  // cell t - 3
+                    const uint32_t sl3 = (u >= 3) ? prv[u - 3] : bef[u];
                     const __amdgpu_buffer_rsrc_t dst = block_rsrc<ST>(D.pool, sl3 & ~NEWFLAG);
                     double nv;
                     if constexpr (ST == VL_F64) {
@@ -430,22 +458,23 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
                     }
                     if constexpr (LAST) {
                         const unsigned long long any = __ballot(nv >= smin);
-                        sflag[t - 3] = any ? 1 : 0;
+                        sflag[w0 + i0 + u - 3] = any ? 1 : 0;
                     }
                 }
+                a3d = aid;
+                a2 = a1;
+                a1 = a;
+                da_prev = da;
+                face_prev = face;
+                Fc_prev = Fc;
+                Ff_prev = Ff;
             }
-            a3d = aid;
-            a2 = a1;
-            a1 = a;
-            da_prev = da;
-            face_prev = face;
-            Fc_prev = Fc;
-            Ff_prev = Ff;
+            wm >>= PFV;
+#pragma unroll
+            for (int i = 0; i < 3; i++) bef[i] = prv[PFV - 3 + i];
+#pragma unroll
+            for (int u = 0; u < PFV; u++) prv[u] = cur[u];
         }
-#pragma unroll
-        for (int i = 0; i < 3; i++) bef[i] = prv[PFV - 3 + i];
-#pragma unroll
-        for (int u = 0; u < PFV; u++) prv[u] = cur[u];
     }
 }
 
@@ -457,8 +486,15 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
 struct VariantInfo {
     int style, pf, minw;
 };
-constexpr VariantInfo VARIANTS[] = {{0, 8, 0}, {0, 8, 6}, {0, 4, 0}, {0, 16, 0}, {1, 8, 0}, {1, 8, 5},
-                                   {2, 8, 0}, {0, 4, 8}, {0, 8, 8}, {2, 8, 8}, {0, 4, 6}};
+// The first is what an untuned partition runs: with the setup's registers out
+// of the marches it fits 64 VGPRs and eight waves per SIMD, and is the fastest
+// or within 2 % of it from 8^3 to 64x64x32 cells in every storage (ms per 1e9
+// cells read and written by the three shears, against the same code with eight
+// cells ahead and no occupancy asked: 16x16x8 FP64 1.98/2.03/2.61 : 2.26/2.31/
+// 3.04, 23x17x11 FP32 1.65/1.30/1.53 : 2.07/1.56/1.90, 64x64x32 FP64 1.97/1.96/
+// 2.06 : 1.96/1.92/2.19, 64x64x32 BF16 mixture 1.07/1.12/1.30 : 1.20/1.28/1.56).
+constexpr VariantInfo VARIANTS[] = {{0, 4, 8}, {0, 8, 6}, {0, 4, 0}, {0, 16, 0}, {1, 8, 0}, {1, 8, 5},
+                                   {2, 8, 0}, {0, 8, 0}, {0, 8, 8}, {2, 8, 8}, {0, 4, 6}};
 constexpr int NVARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
 
 template <int ST, int DIR, bool LAST, int V>
@@ -496,113 +532,172 @@ __device__ __forceinline__ void store_flag_words(const Dev &D, int64_t it, const
     if (lane < D.wlmax) D.masks[it * D.wlmax + lane] = word;
 }
 
-// lowest set bit at position >= from of a MAXWL-word mask, or -1
-__device__ __forceinline__ int first_bit(const uint32_t (&v)[MAXWL], int from)
+// lowest set bit at position >= from of an NM-word mask, or -1
+template <int NM>
+__device__ __forceinline__ int first_bit(const uint64_t (&v)[NM], int from)
 {
 #pragma unroll
-    for (int w = 0; w < MAXWL; w++) {
-        uint32_t x = v[w];
-        if (32 * w + 31 < from) x = 0u;
-        else if (32 * w < from) x &= ~0u << (from - 32 * w);
-        if (x) return 32 * w + __builtin_ctz(x);
+    for (int w = 0; w < NM; w++) {
+        const int f = from - 64 * w;
+        const uint64_t x = v[w] & (f <= 0 ? ~0ull : f < 64 ? ~0ull << (f & 63) : 0ull);
+        if (x) return 64 * w + __builtin_ctzll(x);
     }
     return -1;
 }
 
-__device__ __forceinline__ int last_bit(const uint32_t (&v)[MAXWL])
+template <int NM>
+__device__ __forceinline__ int last_bit(const uint64_t (&v)[NM])
 {
 #pragma unroll
-    for (int w = MAXWL - 1; w >= 0; w--)
-        if (v[w]) return 32 * w + 31 - __builtin_clz(v[w]);
+    for (int w = NM - 1; w >= 0; w--)
+        if (v[w]) return 64 * w + 63 - __builtin_clzll(v[w]);
     return -1;
 }
 
-template <int ST, bool LAST, int V>
+// word w of an NM-word mask moved down by s (0 < s < 64), ones coming in
+template <int NM>
+__device__ __forceinline__ uint64_t down(const uint64_t (&v)[NM], int w, int s)
+{
+    return (v[w] >> s) | ((w + 1 < NM ? v[w + 1 < NM ? w + 1 : w] : ~0ull) << (64 - s));
+}
+
+// an item's place in the row table, presence mask and old ledger item
+template <int NM>
+struct ItemMeta {
+    int32_t id, src;
+    int64_t rowoff;
+    uint64_t m[NM];
+};
+
+template <int ST, int NM>
+__device__ __forceinline__ ItemMeta<NM> load_meta(const Dev &D, const SweepParams &sp, int64_t it)
+{
+    ItemMeta<NM> M;
+    const int32_t *ip = (const int32_t *)(D.items + it);
+    static_assert(sizeof(Item) == 16 && offsetof(Item, id) == 0 && offsetof(Item, rowoff) == 8, "item layout");
+    M.id = scalar_load(ip, 0);
+    M.rowoff = scalar_load((const int64_t *)ip, 1);
+    const uint32_t *mw = D.masks + it * D.wlmax;
+#pragma unroll
+    for (int w = 0; w < NM; w++) {
+        // (words past the mask are not read)
+        const uint32_t lo = scalar_load(mw, min(2 * w, sp.WL - 1)), hi = scalar_load(mw, min(2 * w + 1, sp.WL - 1));
+        M.m[w] = (2 * w < sp.WL ? (uint64_t)lo : 0ull) | (2 * w + 1 < sp.WL ? (uint64_t)hi << 32 : 0ull);
+    }
+    M.src = -1;
+    if constexpr (ST != VL_F64)
+        if (it < sp.lg_cap) M.src = scalar_load(sp.lg_src, it);
+    return M;
+}
+
+// the item's compacted row, lane l the entries l, l + 64, ..
+template <int NM>
+__device__ __forceinline__ void load_row(const Dev &D, const SweepParams &sp, const ItemMeta<NM> &M, int lane,
+                                         uint32_t (&rv)[NM])
+{
+    int n = 0;
+#pragma unroll
+    for (int w = 0; w < NM; w++) n += __popcll(M.m[w]);
+    if (sp.wrap) {  // the row holds the line's own cells
+        n -= __popcll(M.m[0] & 7ull);
+#pragma unroll
+        for (int w = 0; w < NM; w++) {
+            const int f = H + sp.wrap - 64 * w;  // first place past the line
+            n -= __popcll(M.m[w] & (f <= 0 ? ~0ull : f < 64 ? ~0ull << (f & 63) : 0ull));
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NM; k++) rv[k] = lane + 64 * k < n ? (uint32_t)D.rows[M.rowoff + lane + 64 * k] : ABSENT;
+}
+
+// What an item costs beside its march (its index, mask, row and residual: a
+// chain of dependent reads) is taken off the short lines' time by reading the
+// next item's index, mask and residual into scalar registers and its row into
+// a vector register before the current item's march, and by holding the mask
+// as NM 64-bit scalar words (NM by the line's length), on which segments and
+// ranks take a handful of instructions.  With eight 32-bit words for every
+// length and all reads at the item's start the setup was 2/5 of the vector
+// instructions of 24-cell BF16 lines (97 per updated cell, now 72), and the
+// registers it held allowed five waves per SIMD where eight fit now: step of
+// the 24x24x12 BF16 mixture 9.7 -> 7.7 ms, 16x16x8 FP64 2.80 -> 2.36 ms.
+template <int ST, bool LAST, int V, int NM>
 __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
 {
-    __shared__ __align__(16) uint32_t s_slot[4][MAXL + 48];
-    __shared__ uint8_t s_flag[4][MAXL + 48];
-    __shared__ uint32_t s_seg[4][MAXL / 7 + 2];  // segments of the item: first cell | end << 16
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int d = sp.d, L = sp.L, WL = sp.WL;
+    __shared__ __align__(16) uint32_t s_tab[4][TABLE<NM>];
+    __shared__ uint32_t s_row[4][64 * NM];
+    __shared__ uint8_t s_flag[4][64 * NM + 48];
+    __shared__ uint32_t s_seg[4][64 * NM / 7 + 2];  // segments of the item: first cell | end << 16
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int d = sp.d, L = sp.L;
     const int64_t nitems = min((int64_t)D.ctl->n_run[sp.sidx], D.item_cap);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
-    uint32_t *srow = s_slot[wv];
+    uint32_t *srow = s_tab[wv] + WIN0;
     uint32_t *sseg = s_seg[wv];
+    uint8_t *sflag = s_flag[wv];
 
-    for (int64_t it = (int64_t)blockIdx.x * 4 + wv; it < nitems; it += nwaves) {
-        const Item item = D.items[it];
-        // the lane index and the mask words as values of this item (an empty
-        // asm the compiler cannot see through), so the per-lane index
-        // arithmetic and the word tests of the slot table below are
-        // recomputed per item rather than hoisted out of the loop and kept in
-        // registers, which spill at eight waves per SIMD
-        int li = lane, wl = WL;
-        __asm__ volatile("" : "+v"(li), "+s"(wl));
-        // presence of the block along the pencil (wave-uniform), and the
-        // starts of gaps of at least 6 cells without it
-        uint32_t m[MAXWL], gap[MAXWL];
+    int64_t it = (int64_t)blockIdx.x * 4 + wv;
+    if (it >= nitems) return;
+    // no cell before the line and past its mask words
+    const int lane0 = threadIdx.x & 63;
+    if (lane0 < WIN0) s_tab[wv][lane0] = ABSENT;
+    for (int t = 64 * NM + lane0; t < TABLE<NM> - WIN0; t += 64) srow[t] = ABSENT;
+    ItemMeta<NM> M = load_meta<ST, NM>(D, sp, it);
+    uint32_t rv[NM];
+    load_row<NM>(D, sp, M, lane0, rv);
+    double start_sum = take_residual<ST>(sp, M.src);
+    for (; it < nitems; it += nwaves) {
+        // the lane's index as a value of this item (an empty asm the compiler
+        // cannot see through), so per-lane index arithmetic is redone per item
+        // rather than held in registers through the marches
+        int lane = threadIdx.x & 63;
+        __asm__ volatile("" : "+v"(lane));
+        const ItemMeta<NM> N = load_meta<ST, NM>(D, sp, it + nwaves < nitems ? it + nwaves : it);
+        uint64_t any = 0;
+#pragma unroll
+        for (int w = 0; w < NM; w++) any |= M.m[w];
+        double carry = start_sum * (1.0 / BLK);
+        if (any == 0) {  // empty item: no updated cell, the residual passes on
+            leave_residual<ST>(D, sp, it, lane, carry, start_sum);
+            load_row<NM>(D, sp, N, lane, rv);
+            start_sum = take_residual<ST>(sp, N.src);
+            M = N;
+            continue;
+        }
         // per-cell slot table of this item in LDS: slot, slot|NEWFLAG or ABSENT
         {
-            int pre[MAXWL + 1];
-            pre[0] = 0;
 #pragma unroll
-            for (int w = 0; w < MAXWL; w++) {
-                m[w] = (w < wl) ? __builtin_amdgcn_readfirstlane(D.masks[it * D.wlmax + w]) : 0u;
-                pre[w + 1] = pre[w] + __popc(m[w]);
-            }
-            if (pre[MAXWL] == 0) {  // empty item: no updated cell, the residual passes on
-                double sum;
-                const double r = take_residual<ST>(sp, it, sum);
-                leave_residual<ST>(D, sp, it, li, r, sum);
-                continue;
-            }
-#pragma unroll
-            for (int w = 0; w < MAXWL; w++) {
-                const uint32_t a0 = ~m[w], a1 = (w + 1 < MAXWL) ? ~m[w + 1] : ~0u;
-                uint32_t r = a0;
-#pragma unroll
-                for (int k = 1; k < 6; k++) r &= (a0 >> k) | (a1 << (32 - k));
-                gap[w] = r & ((m[w] << 1) | (w > 0 ? m[w - 1] >> 31 : 0u));
-            }
-            // the cells whose slots are in the row (a periodic line's own)
+            for (int k = 0; k < NM; k++) s_row[wv][lane + 64 * k] = rv[k];
+            wave_sync_lds();
+            int base = sp.wrap ? -__popcll(M.m[0] & 7ull) : 0;
             const int c0 = sp.wrap ? H : 0, c1 = sp.wrap ? H + sp.wrap : L;
-            const int left = sp.wrap ? __popc(m[0] & 7u) : 0;
-            const int half = li >> 5, b = li & 31;
 #pragma unroll
-            for (int w = 0; w < MAXWL; w += 2) {
-                if (w < wl) {
-                    const uint32_t mw = half ? m[w + 1] : m[w];
-                    const int base = (half ? pre[w + 1] : pre[w]) - left;
-                    const int t = 32 * (w + half) + b;
-                    if (t < L) {
-                        const bool pr = ((mw >> b) & 1u) && t >= c0 && t < c1;
-                        const int rk = base + __popc(mw & ((1u << b) - 1u));
-                        srow[t] = pr ? (uint32_t)D.rows[item.rowoff + rk] : ABSENT;
-                    }
-                }
+            for (int k = 0; k < NM; k++) {
+                const int t = lane + 64 * k;
+                const bool pr = ((M.m[k] >> lane) & 1ull) && t >= c0 && t < c1;
+                const int rk = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(M.m[k] >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)M.m[k], 0));
+                srow[t] = pr ? s_row[wv][rk] : ABSENT;
+                base += __popcll(M.m[k]);
             }
-            for (int t = L + li; t < L + 40; t += 64) srow[t] = ABSENT;
         }
         wave_sync_lds();
         if (sp.wrap) {
-            wrap_slots<ST>(D, srow, L, sp.wrap, li, 0);
+            wrap_slots<ST>(D, srow, L, sp.wrap, lane, 0);
             wave_sync_lds();
         }
+        // the next item's row and residual, on their way during the march
+        load_row<NM>(D, sp, N, lane, rv);
+        const double next_sum = take_residual<ST>(sp, N.src);
 
         // the block's coordinate along d (the mesh extents passed through an
         // empty asm, so the divisions' reciprocals are formed per item, not
         // kept in registers across items) and the lane's velocity cell in it
         int nb0 = D.nblk[0], nb1 = D.nblk[1];
         __asm__ volatile("" : "+s"(nb0), "+s"(nb1));
-        const int bd = (d == 0) ? item.id % nb0 : (d == 1) ? (item.id / nb0) % nb1 : item.id / (nb0 * nb1);
-        const int ld = (d == 0) ? (li & 3) : (d == 1) ? ((li >> 2) & 3) : (li >> 4);
+        const int bd = (d == 0) ? M.id % nb0 : (d == 1) ? (M.id / nb0) % nb1 : M.id / (nb0 * nb1);
+        const int ld = (d == 0) ? (lane & 3) : (d == 1) ? ((lane >> 2) & 3) : (lane >> 4);
         const double c = courant(D, d, 4 * bd + ld, sp.dt);
         const unsigned long long npos = __ballot(c > 0.0), nneg = __ballot(c < 0.0);
-        double start_sum;
-        double carry = take_residual<ST>(sp, it, start_sum);
-        uint8_t *sflag = s_flag[wv];
         // March each segment of cells holding the block: from its first such
         // cell to three past its last (where the last one is written).  Before
         // a segment's first cell at least 6 cells read as zero, so the
@@ -611,32 +706,46 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
         // The segments are listed in LDS first, so the masks need no
         // registers during the marches.
         int nseg = 0;
-        for (int tb = first_bit(m, 0); tb >= 0;) {
-            const int g = first_bit(gap, tb + 1);
-            const int te = (g >= 0) ? g + 3 : last_bit(m) + 4;
-            if (li == 0) sseg[nseg] = (uint32_t)tb | ((uint32_t)te << 16);
-            nseg++;
-            tb = (g >= 0) ? first_bit(m, g) : -1;
+        {
+            // starts of gaps of at least 6 cells without the block
+            uint64_t z[NM], z2[NM], gap[NM];
+#pragma unroll
+            for (int w = 0; w < NM; w++) z[w] = ~M.m[w];
+#pragma unroll
+            for (int w = 0; w < NM; w++) z2[w] = z[w] & down<NM>(z, w, 1);
+#pragma unroll
+            for (int w = 0; w < NM; w++)
+                gap[w] = z2[w] & down<NM>(z2, w, 2) & down<NM>(z2, w, 4) &
+                         ((M.m[w] << 1) | (w > 0 ? M.m[w > 0 ? w - 1 : 0] >> 63 : 0ull));
+            for (int tb = first_bit<NM>(M.m, 0); tb >= 0;) {
+                const int g = first_bit<NM>(gap, tb + 1);
+                const int te = (g >= 0) ? g + 3 : last_bit<NM>(M.m) + 4;
+                if (lane == 0) sseg[nseg] = (uint32_t)tb | ((uint32_t)te << 16);
+                nseg++;
+                tb = (g >= 0) ? first_bit<NM>(M.m, g) : -1;
+            }
         }
         wave_sync_lds();
         for (int k = 0; k < nseg; k++) {
             const uint32_t v = uniform_u32(sseg[k]);
             const int tb = (int)(v & 0xffffu), te = (int)(v >> 16);
             if (npos == ~0ull)
-                march<ST, 1, LAST, V>(D, srow, sflag, L, c, li, sp.sparse_min, carry, tb, te);
+                march<ST, 1, LAST, V>(D, srow, sflag, L, c, lane, sp.sparse_min, carry, tb, te);
             else if (nneg == ~0ull)
-                march<ST, -1, LAST, V>(D, srow, sflag, L, c, li, sp.sparse_min, carry, tb, te);
+                march<ST, -1, LAST, V>(D, srow, sflag, L, c, lane, sp.sparse_min, carry, tb, te);
             else
-                march<ST, 0, LAST, V>(D, srow, sflag, L, c, li, sp.sparse_min, carry, tb, te);
+                march<ST, 0, LAST, V>(D, srow, sflag, L, c, lane, sp.sparse_min, carry, tb, te);
         }
         if constexpr (LAST) {
             wave_sync_lds();
-            store_flag_words(D, it, srow, sflag, L, li);
+            store_flag_words(D, it, srow, sflag, L, lane);
         }
 
         // the line's final carry (the ledger takes those of the local pencils)
-        leave_residual<ST>(D, sp, it, li, carry, start_sum);
+        leave_residual<ST>(D, sp, it, lane, carry, start_sum);
         wave_sync_lds();
+        M = N;
+        start_sum = next_sum;
     }
 }
 
@@ -813,8 +922,11 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
         const int bd = block_coord(D, d, id);
         const double c = courant(D, d, 4 * bd + ld, sp.dt);
         const unsigned long long npos = __ballot(c > 0.0), nneg = __ballot(c < 0.0);
-        double start_sum;
-        double carry = take_residual<ST>(sp, it, start_sum);
+        int32_t src = -1;
+        if constexpr (ST != VL_F64)
+            if (it < sp.lg_cap) src = sp.lg_src[it];
+        const double start_sum = take_residual<ST>(sp, (int32_t)uniform_u32((uint32_t)src));
+        double carry = start_sum * (1.0 / BLK);
         auto build = [&]() {
             build_slots<ST>(D, nit, nitems, L, WL, sp.wrap, WRAP - place, lane, Y);
             wave_sync_lds();
@@ -838,24 +950,24 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
     }
 }
 
-template <int ST, bool LAST, int V>
+template <int ST, bool LAST, int V, int NM>
 __global__ __launch_bounds__(256) void k_sweep(Dev D, SweepParams sp)
 {
     if (failed(D)) return;  // waves are independent: no barrier to keep
     if constexpr (VARIANTS[V].style == 2)
         sweep_stream<ST, LAST>(D, sp);
     else
-        sweep_body<ST, LAST, V>(D, sp);
+        sweep_body<ST, LAST, V, NM>(D, sp);
 }
 
-template <int ST, bool LAST, int V, int MINW>
+template <int ST, bool LAST, int V, int NM, int MINW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MINW))) void k_sweep_occ(Dev D, SweepParams sp)
 {
     if (failed(D)) return;
     if constexpr (VARIANTS[V].style == 2)
         sweep_stream<ST, LAST>(D, sp);
     else
-        sweep_body<ST, LAST, V>(D, sp);
+        sweep_body<ST, LAST, V, NM>(D, sp);
 }
 
 template <typename K>
@@ -876,17 +988,29 @@ static dim3 persistent_grid(K kernel)
     return dim3((unsigned)std::min(per * ncu, NSINK / 4));
 }
 
-template <int ST, bool LAST, int V>
-static void launch_variant(const Dev &D, const SweepParams &sp, hipStream_t st)
+template <int ST, bool LAST, int V, int NM>
+static void launch_words(const Dev &D, const SweepParams &sp, hipStream_t st)
 {
     constexpr VariantInfo vi = VARIANTS[V];
     if constexpr (vi.minw > 0) {
-        static const dim3 g = persistent_grid(k_sweep_occ<ST, LAST, V, (vi.minw > 0 ? vi.minw : 1)>);
-        hipLaunchKernelGGL((k_sweep_occ<ST, LAST, V, (vi.minw > 0 ? vi.minw : 1)>), g, dim3(256), 0, st, D, sp);
+        static const dim3 g = persistent_grid(k_sweep_occ<ST, LAST, V, NM, (vi.minw > 0 ? vi.minw : 1)>);
+        hipLaunchKernelGGL((k_sweep_occ<ST, LAST, V, NM, (vi.minw > 0 ? vi.minw : 1)>), g, dim3(256), 0, st, D, sp);
     } else {
-        static const dim3 g = persistent_grid(k_sweep<ST, LAST, V>);
-        hipLaunchKernelGGL((k_sweep<ST, LAST, V>), g, dim3(256), 0, st, D, sp);
+        static const dim3 g = persistent_grid(k_sweep<ST, LAST, V, NM>);
+        hipLaunchKernelGGL((k_sweep<ST, LAST, V, NM>), g, dim3(256), 0, st, D, sp);
     }
+}
+
+// the kernel for the line's mask words (the streamed and unconditional
+// variants hold the longest line's)
+template <int ST, bool LAST, int V>
+static void launch_variant(const Dev &D, const SweepParams &sp, hipStream_t st)
+{
+    if constexpr (VARIANTS[V].style == 0) {
+        if (sp.L <= 64) return launch_words<ST, LAST, V, 1>(D, sp, st);
+        if (sp.L <= 128) return launch_words<ST, LAST, V, 2>(D, sp, st);
+    }
+    launch_words<ST, LAST, V, MAXL / 64>(D, sp, st);
 }
 
 template <int ST, bool LAST>

@@ -126,6 +126,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc(void *pool, uint32_
     return __builtin_amdgcn_make_buffer_rsrc((char *)pool + (uint64_t)slot * NB, (short)0, NB, RSRC_WORD3);
 }
 
+// the same, or with no records (every lane reads zero, nothing is fetched)
+template <int ST>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t block_rsrc_if(void *pool, uint32_t slot, bool there)
+{
+    constexpr int NB = 64 * Storage<ST>::BYTES;
+    return __builtin_amdgcn_make_buffer_rsrc((char *)pool + (uint64_t)slot * NB, (short)0, there ? NB : 0, RSRC_WORD3);
+}
+
 // a lane's value of a block: double for FP64 storage, else float
 template <int ST>
 __device__ __forceinline__ auto block_load(__amdgpu_buffer_rsrc_t r, uint32_t off)
