@@ -17,27 +17,33 @@
 //
 // k_accel_factors: per local cell, the three maps (12 doubles) and a flag if a
 //   map cannot be split (its own coefficient not positive).
-// k_accel: one workgroup per local cell runs the three remaps in turn.  Per
-//   remap, along axis d:
-//   * the cell's block set is an LDS bitmap; a block column (fixed block
-//     coordinates across d) spans from its lowest to its highest block,
-//     widened to where its image can reach (the map of the column's extent
-//     with the extreme shifts of its 16 velocity columns, one cell of margin);
-//   * blocks of that span missing from the cell are created: slots from the
-//     free ring, entries merged into the sorted list (in place from the end,
-//     or into a larger place when the list outgrows it);
-//   * the workgroup remaps one block column at a time: it stages the column
-//     in LDS (16 velocity columns x its span, missing blocks as zero; eight
-//     blocks' loads in flight per wavefront), the limited parabola edges of
-//     every cell once (runs of consecutive cells per thread, each slope
-//     computed once), then the new averages, writing every block of the
-//     span, 64 lanes = the block's 64 cells, so loads and stores are
-//     coalesced;
-//   * the last remap leaves per list entry the flags the pruning reads:
-//     bit 0 a value >= the content threshold, bit 1 a nonzero value, bit 2
-//     created by this step.
-//   Blocks created but left all zero are dropped by the pruning (as the new
-//   block set is the old one plus every block holding a nonzero value).
+// Per remap, along axis d, two kernels:
+// k_accel_plan, one workgroup per local cell: a block column (fixed block
+//   coordinates across d) spans from its lowest to its highest block, widened
+//   to where its image can reach (the map of the column's extent with the
+//   extreme shifts of its 16 velocity columns, one cell of margin); blocks of
+//   that span missing from the cell are created: slots from the free ring,
+//   entries merged into the sorted list (in place from the end, or into a
+//   larger place when the list outgrows it).  Every block column becomes a
+//   work item with a row of the list places of its blocks.
+// k_accel_remap, one wavefront per block column, persistent: it stages the
+//   column in LDS in the storage type (16 velocity columns x its span, missing
+//   blocks as zero), then takes the column's faces four cells of sixteen
+//   columns at a time: the departure point of a cell's lower face, the limited
+//   parabola of the source cell it lies in and that parabola's head, once per
+//   face; a cell's new average takes its upper face from the next lane of its
+//   quad (lanes: quad = the 4 cells of a velocity column in the block), so each
+//   head is computed once.  Blocks are read and written whole.
+//   The last remap leaves per list entry the flags the pruning reads: bit 0 a
+//   value >= the content threshold, bit 1 a nonzero value, bit 2 created by
+//   this step.
+// Blocks created but left all zero are dropped by the pruning (as the new
+// block set is the old one plus every block holding a nonzero value).
+// Before, one workgroup took a cell through all three remaps, a block column
+// at a time with three barriers each: hot cells of a mixture (4,400 blocks
+// beside 80) ran long after the rest, and every cell's columns were a serial
+// chain.  Acceleration step with moments, before -> now: 24x24x12 BF16
+// mixture 19.2 -> 7.5 ms, 11x9x7 sparse FP64 1.49 -> 0.79 ms.
 #include <algorithm>
 
 #include "vl_internal.h"
@@ -53,7 +59,9 @@ struct AccelParams {
     int order[3];
     int cur;               // local list region in use
     int ncols;             // block columns of the widest cross-section
-    int hc;                // staging cells per velocity column (4 max nblk)
+    int mx;                // blocks of the longest axis
+    int64_t q0;            // first local cell of this launch
+    uint32_t mg[2];        // ceil(2^32 / nblk[0 / 1]): exact division of block ids (below 2^17, by at most 2^10)
 };
 
 constexpr int ACC_MAP = ACC_MAP_DOUBLES;
@@ -136,77 +144,37 @@ __global__ __launch_bounds__(256) void k_accel_factors(Dev D, AccelParams ap)
 // ---------------------------------------------------------------------------
 // column remap
 // ---------------------------------------------------------------------------
-// limited slope of cell j of a column (CW84 eq. 1.7-1.8) from its average
-// a0 and its neighbours' am, ap: the central difference, limited to twice
-// either one-sided difference, zero at an extremum
-__device__ __forceinline__ double col_slope(double am, double a0, double ap)
+// twice the limited slope of a cell (CW84 eq. 1.7-1.8) from its one-sided
+// differences dl, dr (given as x4, scaled exactly) and their sum c: c limited
+// to four times either difference, zero at an extremum
+__device__ __forceinline__ double col_slope2(double dl4, double dr4, double c)
 {
-    const double dl = a0 - am, dr = ap - a0;
-    const double central = 0.5 * (ap - am);
-    const double m = fmin(fabs(central), fmin(2.0 * fabs(dl), 2.0 * fabs(dr)));
-    return (dr * dl > 0.0) ? copysign(m, central) : 0.0;
+    const double up = fmax(0.0, fmin(fmin(dl4, dr4), c));  // c > 0
+    const double dn = fmin(0.0, fmax(fmax(dl4, dr4), c));  // c < 0
+    return up + dn;                                        // (one of them is zero)
 }
 
-// limited parabola edges (l, r) of a cell from its average a0, its
-// neighbours' am, ap and the limited slopes dm, d0, dp of cells j-1, j, j+1
-// (CW84 eq. 1.6 faces, then the eq. 1.10 limiter)
-__device__ __forceinline__ void col_edges(double am, double a0, double ap, double dm, double d0, double dp,
-                                          double &l, double &r)
+// CW84 eq. 1.10 on the face offsets: x limited to twice the other side's
+// offset y, zero unless they share a sign
+__device__ __forceinline__ double col_offset(double x, double y)
 {
-    constexpr double SIXTH = 1.0 / 6.0;
-    l = am + 0.5 * (a0 - am) - (d0 - dm) * SIXTH;
-    r = a0 + 0.5 * (ap - a0) - (dp - d0) * SIXTH;
-    if ((r - a0) * (a0 - l) <= 0.0) {
-        l = a0;
-        r = a0;
-    } else {
-        const double dd = r - l;
-        const double mm = a0 - 0.5 * (l + r);
-        if (dd * mm > dd * dd * SIXTH)
-            l = 3.0 * a0 - 2.0 * r;
-        else if (-(dd * dd) * SIXTH > dd * mm)
-            r = 3.0 * a0 - 2.0 * l;
-    }
+    return copysign(fmax(0.0, fmin(fabs(x), copysign(2.0, x) * y)), x);
 }
 
-// mass of source cell j's limited parabola (average a0, edges l, r: CW84
-// eq. 1.10's profile) over [0, x] of the cell (0 <= x <= 1, cell units)
-__device__ __forceinline__ double col_head(double a0, double l, double r, double x)
+// Mass of a source cell's limited parabola over [0, x] of the cell (0 <= x <=
+// 1, cell units), from the averages of the five cells around it.  The face
+// offsets dL = a - a_L, dR = a_R - a (CW84 eq. 1.6 faces) are formed from the
+// differences, limited, and put into eq. 1.5's profile, whose integral is
+//   x (a - dL + x (2 dL - dR - x (dL - dR))).
+__device__ __forceinline__ double col_head(double am2, double am, double a0, double ap, double ap2, double x)
 {
-    constexpr double THIRD = 1.0 / 3.0;
-    const double a6 = 6.0 * (a0 - 0.5 * (l + r));
-    const double q = 0.5 * ((r - l) + a6);
-    return x * (l + x * (q - x * a6 * THIRD));
-}
-
-// new average of cell i of a column moved by u -> alpha u + sigma (inv_alpha =
-// 1 / alpha): the mass of its pre-image [(i - sigma)/alpha, (i + 1 - sigma)/alpha]
-// under the source parabolas, as the tail of the first source cell it meets
-// (the cell's average minus its head), the averages of the cells it covers
-// whole, and the head of the last; cells outside [base, base + ncell) (the
-// staged span) hold zero, and so does all of the mesh beyond it
-template <typename A, typename E>
-__device__ __forceinline__ double col_remap_cell(const A &a, const E &edges, int base, int ncell, int i,
-                                                 double inv_alpha, double sigma)
-{
-    double lo = ((double)i - sigma) * inv_alpha, hi = ((double)i + 1.0 - sigma) * inv_alpha;
-    if (!(hi > (double)base) || !(lo < (double)(base + ncell))) return 0.0;
-    lo = fmax(lo, (double)(base - 1));
-    hi = fmin(hi, (double)(base + ncell + 1));
-    const double fl = floor(lo), fh = floor(hi);
-    const int j0 = (int)fl, j1 = (int)fh;
-    const double xa = lo - fl, xb = hi - fh;
-    double l, r;
-    edges(j0, l, r);
-    const double a0 = a(j0);
-    if (j0 == j1) return col_head(a0, l, r, xb) - col_head(a0, l, r, xa);
-    double m = a0 - col_head(a0, l, r, xa);
-    for (int j = j0 + 1; j < j1; j++) m += a(j);
-    if (xb > 0.0) {
-        edges(j1, l, r);
-        m += col_head(a(j1), l, r, xb);
-    }
-    return m;
+    constexpr double TWELFTH = 1.0 / 12.0;
+    const double g0 = am - am2, g1 = a0 - am, g2 = ap - a0, g3 = ap2 - ap;
+    const double h0 = 4.0 * g0, h1 = 4.0 * g1, h2 = 4.0 * g2, h3 = 4.0 * g3;
+    const double dm = col_slope2(h0, h1, a0 - am2), d0 = col_slope2(h1, h2, ap - am), dp = col_slope2(h2, h3, ap2 - a0);
+    const double dL = fma(0.5, g1, (d0 - dm) * TWELFTH), dR = fma(0.5, g2, (d0 - dp) * TWELFTH);
+    const double l = col_offset(dL, dR), r = col_offset(dR, dL);
+    return x * fma(x, fma(-x, l - r, fma(2.0, l, -r)), a0 - l);
 }
 
 // shift sigma (cell units) of the velocity column at transverse velocity
@@ -236,68 +204,66 @@ __device__ inline int rank_of(const uint32_t *bm, const int *rk, int32_t id)
     return rk[id >> 5] + __popc(bm[id >> 5] & ((1u << (id & 31)) - 1u));
 }
 
-// exclusive scan of a[0..n) in place by the workgroup; returns the total
-__device__ int acc_scan(int *a, int n, int *s_tmp)
+// inclusive sums of v over the workgroup's threads before and with this one;
+// the total of all in `total` (s_w: one entry per wavefront)
+__device__ __forceinline__ int block_incl(int v, int *s_w, int &total)
 {
-    const int tid = threadIdx.x;
-    const int per = (n + 255) / 256;
-    const int b = min(tid * per, n), e = min(b + per, n);
-    int sum = 0;
-    for (int i = b; i < e; i++) sum += a[i];
-    s_tmp[tid] = sum;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const int v = (tid >= o) ? s_tmp[tid - o] : 0;
-        __syncthreads();
-        s_tmp[tid] += v;
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(v, o);
+        if (lane >= o) v += u;
     }
-    int run = s_tmp[tid] - sum;
-    const int total = s_tmp[255];
-    for (int i = b; i < e; i++) {
-        const int v = a[i];
-        a[i] = run;
-        run += v;
-    }
+    if (lane == 63) s_w[wv] = v;
     __syncthreads();
-    return total;
+    total = 0;
+    for (int w = 0; w < 4; w++) {
+        const int t = s_w[w];
+        v += w < wv ? t : 0;
+        total += t;
+    }
+    return v;
 }
 
-template <int ST>
-__global__ __launch_bounds__(256) void k_accel(Dev D, AccelParams ap)
+// a row entry: the block's place in the cell's list, created in this step
+// (zero in the cell's state before it) and in this remap (reads as zero)
+constexpr uint32_t ROW_PLACE = 0x3ffff, ROW_STEP = 0x40000000u, ROW_NEW = 0x80000000u;
+static_assert(NB_MAX <= 0x40000, "list place in a row entry");
+
+// a work item's block column: lowest and highest block and the column's number
+__device__ inline int32_t pack_column(int col, int lo, int hi) { return col | (lo << 12) | (hi << 18); }
+static_assert(ACC_MAX_NBLK <= 64, "six bits a block coordinate");
+
+// Bound by latency: a dozen barriers and four dependent reads of the list.
+// Spans come from one LDS minimum, maximum and count per list entry, not from
+// a test of every block of the mesh.
+__global__ __launch_bounds__(256) void k_accel_plan(Dev D, AccelParams ap, int k)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int s_tmp[256];
-    __shared__ double s_map[ACC_MAP];
-    __shared__ int s_cnt[4];
+    __shared__ int s_w[4][4];
+    __shared__ int s_cnt[2];
     __shared__ long long s_at[2];
-    __shared__ unsigned long long s_ring;
+    __shared__ unsigned long long s_base[3];
     __shared__ int s_fail;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x;
     const int W = D.W;
-    uint32_t *s_bm = (uint32_t *)smem;     // current block set
-    uint32_t *s_old = s_bm + W;            // the set before this remap
-    uint32_t *s_start = s_old + W;         // the set before this step
-    int *s_rank = (int *)(s_start + W);    // W + 1
-    int *s_span = s_rank + (W + 1);        // per block column: lo | hi << 16, or -1
-    int *s_new = s_span + ap.ncols;        // per block column: blocks created (then their prefix)
-    // per wavefront: the block column it remaps, 16 velocity columns of
-    // hc + 1 cells (odd stride: fewer bank conflicts), and the slots of the
-    // column's blocks
-    // (byte offsets from the LDS array itself, so the compiler keeps these
-    // pointers in the LDS address space): the block column being remapped,
-    // averages and limited edges of 16 velocity columns of hc + 1 cells (odd
-    // stride: fewer bank conflicts)
-    const int hcs = ap.hc + 1;
-    const int stage_off = (4 * (3 * W + (W + 1) + 2 * ap.ncols) + 15) & ~15;
-    double *s_a = (double *)(smem + stage_off);
-    double *s_l = s_a + 16 * hcs;
-    double *s_r = s_l + 16 * hcs;
+    uint32_t *s_bm = (uint32_t *)smem;     // block set after this remap's creations
+    uint32_t *s_old = s_bm + W;            // and before
+    int *s_rank = (int *)(s_old + W);      // W + 1
+    int *s_lo = s_rank + (W + 1);          // per block column: lowest block, then lo | hi << 16, or -1
+    int *s_hi = s_lo + ap.ncols;           // highest block, then blocks to create
+    int *s_len = s_hi + ap.ncols;          // blocks held, then row entries before it
 
-    const int64_t q = blockIdx.x;
+    const int64_t q = ap.q0 + blockIdx.x;
     const int x = (int)(q % D.n[0]), y = (int)((q / D.n[0]) % D.n[1]), z = (int)(q / ((int64_t)D.n[0] * D.n[1]));
     const int64_t c = cell_index(D, x + H, y + H, z + H);
-    if (tid < ACC_MAP) s_map[tid] = ap.maps[ACC_MAP * q + tid];
+    const int d = ap.order[k];
+    const int e1 = (d == 0) ? 1 : 0, e2 = (d == 2) ? 1 : 2;
+    const int nbd = D.nblk[d], nb1 = D.nblk[e1], nb2 = D.nblk[e2];
+    const int N = 4 * nbd;
+    const int ncol = nb1 * nb2;
+    double row[4];
+    for (int j = 0; j < 4; j++) row[j] = ap.maps[ACC_MAP * q + 4 * k + j];
+    const double alpha = row[d];
     if (tid == 0) {
         s_fail = failed(D) ? 1 : 0;
         s_at[0] = D.lstart[c];
@@ -305,263 +271,371 @@ __global__ __launch_bounds__(256) void k_accel(Dev D, AccelParams ap)
         s_cnt[1] = D.lcapa[c];
     }
     for (int w = tid; w < W; w += 256) s_bm[w] = 0u;
+    for (int col = tid; col < ncol; col += 256) {
+        s_lo[col] = nbd;
+        s_hi[col] = -1;
+        s_len[col] = 0;
+    }
     __syncthreads();
     if (s_fail) return;
-    {
-        const int cnt = s_cnt[0];
-        const int64_t cs = s_at[0];
-        for (int e = tid; e < cnt; e += 256) {
-            const int32_t id = D.lid[cs + e];
-            atomicOr(&s_bm[id >> 5], 1u << (id & 31));
+    const int cnt = s_cnt[0], cap = s_cnt[1];
+    const int64_t cs = s_at[0];
+    // block coordinates along d and across
+    auto place = [&](int32_t id, int &bd) -> int {
+        const int r = D.nblk[0] > 1 ? (int)__umulhi((uint32_t)id, ap.mg[0]) : id;
+        const int b2 = D.nblk[1] > 1 ? (int)__umulhi((uint32_t)r, ap.mg[1]) : r;
+        const int b0 = id - r * D.nblk[0], b1 = r - b2 * D.nblk[1];
+        bd = d == 0 ? b0 : d == 1 ? b1 : b2;
+        return (e1 == 0 ? b0 : b1) + nb1 * (e2 == 1 ? b1 : b2);
+    };
+    // 1. block set, and per column its extent and count
+    constexpr int MU = 4;  // entries a thread takes at a time, their loads together
+    for (int e0 = tid; e0 < cnt; e0 += 256 * MU) {
+        int32_t id[MU];
+#pragma unroll
+        for (int u = 0; u < MU; u++) id[u] = e0 + 256 * u < cnt ? D.lid[cs + e0 + 256 * u] : -1;
+#pragma unroll
+        for (int u = 0; u < MU; u++) {
+            if (id[u] < 0) continue;
+            int bd;
+            const int col = place(id[u], bd);
+            atomicOr(&s_bm[id[u] >> 5], 1u << (id[u] & 31));
+            atomicMin(&s_lo[col], bd);
+            atomicMax(&s_hi[col], bd);
+            atomicAdd(&s_len[col], 1);
         }
     }
     __syncthreads();
-    for (int w = tid; w < W; w += 256) s_start[w] = s_bm[w];
-
-    const int lx = lane & 3, ly = (lane >> 2) & 3, lz = lane >> 4;
-    for (int k = 0; k < 3; k++) {
-        const int d = ap.order[k];
-        const int e1 = (d == 0) ? 1 : 0, e2 = (d == 2) ? 1 : 2;
-        const int nbd = D.nblk[d], nb1 = D.nblk[e1], nb2 = D.nblk[e2];
-        const int N = 4 * nbd;
-        const int ncol = nb1 * nb2;
-        const double *row = s_map + 4 * k;
-        const double alpha = row[d];
-        for (int w = tid; w < W; w += 256) s_old[w] = s_bm[w];
-        __syncthreads();
-        // 1. span of every block column and the blocks it lacks
-        for (int col = tid; col < ncol; col += 256) {
-            const int b1 = col % nb1, b2 = col / nb1;
-            int bmin = -1, bmax = -1;
-            for (int bd = 0; bd < nbd; bd++)
-                if (has_bit(s_bm, compose_id(D, d, e1, e2, bd, b1, b2))) {
-                    if (bmin < 0) bmin = bd;
-                    bmax = bd;
-                }
-            if (bmin < 0) {
-                s_span[col] = -1;
-                s_new[col] = 0;
-                continue;
-            }
-            // extreme shifts: sigma is affine in the velocity column, so at
-            // the corners of the block column's 4 x 4
-            double smin = 1e300, smax = -1e300;
-            for (int u = 0; u < 4; u++) {
-                const double s = col_sigma(D, row, d, e1, e2, 4 * b1 + 3 * (u & 1), 4 * b2 + 3 * (u >> 1));
-                smin = fmin(smin, s);
-                smax = fmax(smax, s);
-            }
-            // cells that can receive mass from [4 bmin, 4 bmax + 4): those
-            // with alpha u0 + sigma - 1 < i < alpha u1 + sigma (a cell of margin)
-            const double ilo = floor(alpha * (4.0 * bmin) + smin) - 1.0;
-            const double ihi = ceil(alpha * (4.0 * bmax + 4.0) + smax);
-            int lo = bmin, hi = bmax;
-            if (ihi >= 0.0 && ilo <= (double)(N - 1)) {
-                const int i0 = (int)fmax(ilo, 0.0), i1 = (int)fmin(ihi, (double)(N - 1));
-                lo = min(lo, i0 >> 2);
-                hi = max(hi, i1 >> 2);
-            }
-            int nn = 0;
-            for (int bd = lo; bd <= hi; bd++) nn += has_bit(s_bm, compose_id(D, d, e1, e2, bd, b1, b2)) ? 0 : 1;
-            s_span[col] = lo | (hi << 16);
-            s_new[col] = nn;
+    for (int w = tid; w < W; w += 256) s_old[w] = s_bm[w];
+    // 2. spans; a thread takes a run of consecutive columns
+    const int per = (ncol + 255) / 256;
+    const int c0 = min(tid * per, ncol), c1 = min(c0 + per, ncol);
+    int my_new = 0, my_row = 0, my_items = 0;
+    for (int col = c0; col < c1; col++) {
+        const int bmin = s_lo[col], bmax = s_hi[col], have = s_len[col];
+        if (have == 0) {
+            s_lo[col] = -1;
+            s_hi[col] = 0;
+            continue;
         }
-        __syncthreads();
-        const int T = acc_scan(s_new, ncol, s_tmp);
-        // 2. places: slots for the created blocks, a larger list place if needed
-        if (tid == 0) {
-            const int cnt = s_cnt[0], cap = s_cnt[1];
-            unsigned long long err = 0;
-            s_at[1] = s_at[0];
-            if (T > 0) {
-                const unsigned long long nb = atomicAdd(&D.ctl->ring_head, (unsigned long long)T);
-                if (nb + T > D.ctl->ring_limit) err |= E_RING;
-                s_ring = nb;
-                if (cnt + T > cap) {
-                    const int ncap = (cnt + T) + (cnt + T) / 2 + 32;
-                    const unsigned long long nb0 = atomicAdd(&D.ctl->list_top[ap.cur], (unsigned long long)ncap);
-                    if ((int64_t)(nb0 + ncap) > D.reg_cap[ap.cur]) err |= E_LOCAL_LIST;
-                    s_at[1] = D.reg_off[ap.cur] + (int64_t)nb0;
-                    s_cnt[1] = ncap;
-                }
-            }
-            if (err) atomicOr(&D.ctl->err, err);
-            s_fail = err ? 1 : 0;
+        const int b1 = col % nb1, b2 = col / nb1;
+        // extreme shifts: sigma is affine in the velocity column, so at
+        // the corners of the block column's 4 x 4
+        double smin = 1e300, smax = -1e300;
+        for (int u = 0; u < 4; u++) {
+            const double s = col_sigma(D, row, d, e1, e2, 4 * b1 + 3 * (u & 1), 4 * b2 + 3 * (u >> 1));
+            smin = fmin(smin, s);
+            smax = fmax(smax, s);
         }
-        __syncthreads();
-        if (s_fail) return;  // the partition is reported as failed; nothing is read again
-        const int64_t cs = s_at[0], ns = s_at[1];
-        const int cnt = s_cnt[0];
+        // cells that can receive mass from [4 bmin, 4 bmax + 4): those
+        // with alpha u0 + sigma - 1 < i < alpha u1 + sigma (a cell of margin)
+        const double ilo = floor(alpha * (4.0 * bmin) + smin) - 1.0;
+        const double ihi = ceil(alpha * (4.0 * bmax + 4.0) + smax);
+        int lo = bmin, hi = bmax;
+        if (ihi >= 0.0 && ilo <= (double)(N - 1)) {
+            const int i0 = (int)fmax(ilo, 0.0), i1 = (int)fmin(ihi, (double)(N - 1));
+            lo = min(lo, i0 >> 2);
+            hi = max(hi, i1 >> 2);
+        }
+        const int len = hi - lo + 1;
+        s_lo[col] = lo | (hi << 16);
+        s_hi[col] = len - have;
+        s_len[col] = len;
+        my_new += len - have;
+        my_row += len;
+        my_items++;
+    }
+    int T, R, I;
+    block_incl(my_new, s_w[0], T);
+    int run_row = block_incl(my_row, s_w[1], R) - my_row;
+    int run_item = block_incl(my_items, s_w[2], I) - my_items;
+    // 3. places: items and rows, slots for the created blocks, a larger list
+    //    place if needed
+    if (tid == 0) {
+        unsigned long long err = 0;
+        s_at[1] = cs;
+        s_base[0] = I > 0 ? atomicAdd(&D.ctl->acc_items[k], (unsigned long long)I) : 0ull;
+        s_base[1] = R > 0 ? atomicAdd(&D.ctl->acc_rows[k], (unsigned long long)R) : 0ull;
+        s_base[2] = 0ull;
+        if ((int64_t)(s_base[0] + I) > D.item_cap) err |= E_ITEMS;  // (not reached: launch_accel sizes its launches)
+        if ((int64_t)(s_base[1] + R) > D.row_cap) err |= E_ROWS;    // (not reached: rows hold blocks with slots)
         if (T > 0) {
-            // 3. the created blocks join the set; the list is merged in id
-            //    order (old entries move up to their new rank, from the end
-            //    so that no entry is overwritten before it is read)
-            for (int col = tid; col < ncol; col += 256) {
-                const int sp = s_span[col];
-                if (sp < 0) continue;
+            const unsigned long long nb = atomicAdd(&D.ctl->ring_head, (unsigned long long)T);
+            if (nb + T > D.ctl->ring_limit) err |= E_RING;
+            s_base[2] = nb;
+            if (cnt + T > cap) {
+                const int ncap = (cnt + T) + (cnt + T) / 2 + 32;
+                const unsigned long long nb0 = atomicAdd(&D.ctl->list_top[ap.cur], (unsigned long long)ncap);
+                if ((int64_t)(nb0 + ncap) > D.reg_cap[ap.cur]) err |= E_LOCAL_LIST;
+                s_at[1] = D.reg_off[ap.cur] + (int64_t)nb0;
+                s_cnt[1] = ncap;
+            }
+        }
+        // (a full ring is the error to report where rows are short as well)
+        if (err & E_RING) err &= ~(unsigned long long)E_ROWS;
+        if (err) atomicOr(&D.ctl->err, err);
+        s_fail = err ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_fail) return;  // the partition is reported as failed; nothing is read again
+    const int64_t ns = s_at[1];
+    const int64_t rb = (int64_t)s_base[1];
+    for (int col = c0; col < c1; col++) {
+        const int sp = s_lo[col], nw = s_hi[col], len = s_len[col];
+        s_len[col] = run_row;
+        if (sp >= 0) {
+            Item it;
+            it.id = pack_column(col, sp & 0xffff, sp >> 16);
+            it.pencil = (int32_t)q;
+            it.rowoff = rb + run_row;
+            D.items[(int64_t)s_base[0] + run_item] = it;
+            run_item++;
+            run_row += len;
+            if (nw > 0) {  // the created blocks join the set
                 const int b1 = col % nb1, b2 = col / nb1;
                 for (int bd = sp & 0xffff; bd <= (sp >> 16); bd++) {
                     const int32_t id = compose_id(D, d, e1, e2, bd, b1, b2);
                     if (!has_bit(s_old, id)) atomicOr(&s_bm[id >> 5], 1u << (id & 31));
                 }
             }
-            __syncthreads();
-            for (int w = tid; w < W; w += 256) s_rank[w] = __popc(s_bm[w]);
-            __syncthreads();
-            acc_scan(s_rank, W, s_tmp);
-            for (int e_hi = cnt; e_hi > 0; e_hi -= 256) {
-                const int e = e_hi - 1 - tid;
-                int32_t id = 0, slot = 0;
-                if (e >= 0) {
-                    id = D.lid[cs + e];
-                    slot = D.lslot[cs + e];
-                }
-                __syncthreads();
-                if (e >= 0) {
-                    const int pos = rank_of(s_bm, s_rank, id);
-                    if (ns != cs || pos != e) {
-                        D.lid[ns + pos] = id;
-                        D.lslot[ns + pos] = slot;
-                    }
-                }
-                __syncthreads();
-            }
-            for (int col = tid; col < ncol; col += 256) {
-                const int sp = s_span[col];
-                if (sp < 0) continue;
-                const int b1 = col % nb1, b2 = col / nb1;
-                int kk = s_new[col];
-                for (int bd = sp & 0xffff; bd <= (sp >> 16); bd++) {
-                    const int32_t id = compose_id(D, d, e1, e2, bd, b1, b2);
-                    if (has_bit(s_old, id)) continue;
-                    const int32_t slot = D.ring[(int64_t)((s_ring + kk) % (unsigned long long)D.lcap)];
-                    kk++;
-                    const int pos = rank_of(s_bm, s_rank, id);
-                    D.lid[ns + pos] = id;
-                    D.lslot[ns + pos] = slot;
-                }
-            }
-            __syncthreads();
-            if (tid == 0) {
-                s_cnt[0] = cnt + T;
-                s_at[0] = ns;
-                D.lstart[c] = ns;
-                D.lcount[c] = cnt + T;
-                D.lcapa[c] = s_cnt[1];
-                D.lsorted[c] = cnt + T;
-            }
-        } else {
-            for (int w = tid; w < W; w += 256) s_rank[w] = __popc(s_bm[w]);
-            __syncthreads();
-            acc_scan(s_rank, W, s_tmp);
         }
-        // 4. remap the block columns one at a time, the workgroup together:
-        //    wavefront w stages the blocks lo + w, lo + w + 4, .. (slots and
-        //    values of up to eight in flight together), the workgroup computes
-        //    the limited edges of every cell once, then wavefront w writes the
-        //    new averages of its blocks (64 lanes = a block's 64 cells)
-        const bool last = k == 2;
-        const double inv_alpha = 1.0 / alpha;
-        const int ld = (d == 0) ? lx : (d == 1) ? ly : lz;
-        const int l1 = (e1 == 0) ? lx : ly, l2 = (e2 == 1) ? ly : lz;
-        const int cc = l1 + 4 * l2;
-        for (int col = 0; col < ncol; col++) {
-            const int sp = s_span[col];
-            if (sp < 0) continue;
-            const int lo = sp & 0xffff, hi = sp >> 16;
-            const int b1 = col % nb1, b2 = col / nb1;
-            const int ncell = 4 * (hi - lo + 1);
-            const int nmine = (hi - lo >= wv) ? (hi - lo - wv) / 4 + 1 : 0;  // blocks of this wavefront
-            // lane u finds the slot of the wavefront's block u (at most
-            // hc / 16 + 1 < 64 of them): negative if the block was created in
-            // this remap (it reads as zero)
-            int32_t code = -1;
-            if (lane < nmine) {
-                const int32_t id = compose_id(D, d, e1, e2, lo + wv + 4 * lane, b1, b2);
-                const int32_t slot = D.lslot[ns + rank_of(s_bm, s_rank, id)];
-                code = has_bit(s_old, id) ? slot : -1 - slot;
-            }
-            for (int u0 = 0; u0 < nmine; u0 += 8) {
-                double v[8];
+    }
+    __syncthreads();
+    // row entry of the block of list place pos
+    auto put_row = [&](int32_t id, int pos, uint32_t flags) {
+        int bd;
+        const int col = place(id, bd);
+        D.rows[rb + s_len[col] + (bd - (s_lo[col] & 0xffff))] = (int32_t)((uint32_t)pos | flags);
+    };
+    if (T == 0) {
+        for (int e0 = tid; e0 < cnt; e0 += 256 * MU) {
+            int32_t id[MU], fl[MU];
 #pragma unroll
-                for (int u = 0; u < 8; u++) {
-                    v[u] = 0.0;
-                    if (u0 + u < nmine) {
-                        const int32_t sl = __builtin_amdgcn_readlane(code, u0 + u);
-                        if (sl >= 0) v[u] = Storage<ST>::load(D.pool, (int64_t)sl * BLK + lane);
-                    }
-                }
+            for (int u = 0; u < MU; u++) {
+                const int e = e0 + 256 * u;
+                id[u] = e < cnt ? D.lid[cs + e] : -1;
+                fl[u] = e < cnt && k > 0 ? D.litem[cs + e] : 0;
+            }
 #pragma unroll
-                for (int u = 0; u < 8; u++)
-                    if (u0 + u < nmine) s_a[cc * hcs + 4 * (wv + 4 * (u0 + u)) + ld] = v[u];
+            for (int u = 0; u < MU; u++) {
+                if (id[u] < 0) continue;
+                const int e = e0 + 256 * u;
+                if (k == 0) D.litem[cs + e] = 0;  // bit 2: created in this step
+                put_row(id[u], e, (fl[u] & 4) ? ROW_STEP : 0u);
             }
-            __syncthreads();
-            const int base = 4 * lo;
-            {
-                // thread (velocity column tc, run q) takes the run of
-                // consecutive cells [j0, j1) of its column with a sliding
-                // window, so each cell's limited slope is computed once
-                const int tc = tid & 15, q = tid >> 4;
-                const int per = (ncell + 15) >> 4;
-                const int j0 = q * per, j1 = min(j0 + per, ncell);
-                const double *ac = s_a + tc * hcs;
-                auto A = [&](int j) -> double { return (j >= 0 && j < ncell) ? ac[j] : 0.0; };
-                if (j0 < j1) {
-                    double am = A(j0 - 1), a0 = A(j0), ap = A(j0 + 1);
-                    double dm = col_slope(A(j0 - 2), am, a0), d0 = col_slope(am, a0, ap);
-                    for (int j = j0; j < j1; j++) {
-                        const double app = A(j + 2);
-                        const double dp = col_slope(a0, ap, app);
-                        double l, r;
-                        col_edges(am, a0, ap, dm, d0, dp, l, r);
-                        s_l[tc * hcs + j] = l;
-                        s_r[tc * hcs + j] = r;
-                        am = a0;
-                        a0 = ap;
-                        ap = app;
-                        dm = d0;
-                        d0 = dp;
-                    }
-                }
-            }
-            __syncthreads();
-            {
-                const double *ac = s_a + cc * hcs, *lc = s_l + cc * hcs, *rc = s_r + cc * hcs;
-                // cells outside the span hold zero: flat zero parabolas
-                auto a = [&](int jj) -> double {
-                    const int q = jj - base;
-                    return (q >= 0 && q < ncell) ? ac[q] : 0.0;
-                };
-                auto edges = [&](int jj, double &l, double &r) {
-                    const int q = jj - base;
-                    const bool in = q >= 0 && q < ncell;
-                    l = in ? lc[q] : 0.0;
-                    r = in ? rc[q] : 0.0;
-                };
-                const double sigma = col_sigma(D, row, d, e1, e2, 4 * b1 + l1, 4 * b2 + l2);
-                for (int u = 0; u < nmine; u++) {
-                    const int bd = lo + wv + 4 * u;
-                    const int32_t sl = __builtin_amdgcn_readlane(code, u);
-                    const int32_t slot = sl >= 0 ? sl : -1 - sl;
-                    const double v = col_remap_cell(a, edges, base, ncell, 4 * bd + ld, inv_alpha, sigma);
-                    Storage<ST>::store(D.pool, (int64_t)slot * BLK + lane, v);
-                    if (last) {
-                        const int32_t id = compose_id(D, d, e1, e2, bd, b1, b2);
-                        const double sv = Storage<ST>::round(v);
-                        const bool content = sv >= D.sparse_min, nz = sv != 0.0;
-                        const unsigned long long bc = __ballot(content), bz = __ballot(nz);
-                        if (lane == 0)
-                            D.litem[ns + rank_of(s_bm, s_rank, id)] =
-                                (bc ? 1 : 0) | (bz ? 2 : 0) | (has_bit(s_start, id) ? 0 : 4);
-                    }
-                }
-            }
-            __syncthreads();
         }
+        return;
+    }
+    // 4. ranks; the list is merged in id order (old entries move up to their
+    //    new rank, from the end so that no entry is overwritten before it is
+    //    read)
+    {
+        const int perw = (W + 255) / 256;
+        const int w0 = min(tid * perw, W), w1 = min(w0 + perw, W);
+        int sum = 0, total;
+        for (int w = w0; w < w1; w++) sum += __popc(s_bm[w]);
+        int run = block_incl(sum, s_w[3], total) - sum;
+        for (int w = w0; w < w1; w++) {
+            s_rank[w] = run;
+            run += __popc(s_bm[w]);
+        }
+    }
+    __syncthreads();
+    for (int e_hi = cnt; e_hi > 0; e_hi -= 256 * MU) {
+        int32_t id[MU], slot[MU], fl[MU];
+#pragma unroll
+        for (int u = 0; u < MU; u++) {
+            const int e = e_hi - 1 - tid - 256 * u;
+            id[u] = e >= 0 ? D.lid[cs + e] : -1;
+            slot[u] = e >= 0 ? D.lslot[cs + e] : 0;
+            fl[u] = e >= 0 && k > 0 ? D.litem[cs + e] : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MU; u++) {
+            if (id[u] < 0) continue;
+            const int pos = rank_of(s_bm, s_rank, id[u]);
+            D.lid[ns + pos] = id[u];
+            D.lslot[ns + pos] = slot[u];
+            D.litem[ns + pos] = fl[u];
+            put_row(id[u], pos, (fl[u] & 4) ? ROW_STEP : 0u);
+        }
+        __syncthreads();
+    }
+    // the created blocks, a thread the words w0 .. w1 - 1 of the set: the
+    // slots in id order
+    {
+        const int perw = (W + 255) / 256;
+        const int w0 = min(tid * perw, W), w1 = min(w0 + perw, W);
+        int sum = 0, total;
+        for (int w = w0; w < w1; w++) sum += __popc(s_bm[w] & ~s_old[w]);
+        unsigned long long kk = s_base[2] + (unsigned long long)(block_incl(sum, s_w[0], total) - sum);
+        for (int w = w0; w < w1; w++) {
+            const uint32_t bm = s_bm[w];
+            uint32_t cr = bm & ~s_old[w];
+            while (cr) {
+                const int bit = __ffs(cr) - 1;
+                cr &= cr - 1;
+                const int pos = s_rank[w] + __popc(bm & ((1u << bit) - 1u));
+                D.lid[ns + pos] = 32 * w + bit;
+                D.lslot[ns + pos] = D.ring[(int64_t)(kk % (unsigned long long)D.lcap)];
+                D.litem[ns + pos] = 4;
+                kk++;
+                put_row(32 * w + bit, pos, ROW_NEW | ROW_STEP);
+            }
+        }
+    }
+    if (tid == 0) {
+        D.lstart[c] = ns;
+        D.lcount[c] = cnt + T;
+        D.lcapa[c] = s_cnt[1];
+        D.lsorted[c] = cnt + T;
     }
 }
 
-// LDS of k_accel for a velocity mesh, or 0 if the mesh is beyond its limits
+__device__ inline void acc_wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// the value of the next lane of the quad, the quad's first lane giving `wrap`
+// to its last
+__device__ __forceinline__ int quad_next(int v, int wrap, bool first)
+{
+    return __builtin_amdgcn_mov_dpp(first ? wrap : v, 0x39, 0xf, 0xf, true);  // quad_perm 1 2 3 0
+}
+__device__ __forceinline__ double quad_next(double v, double wrap, bool first)
+{
+    const uint64_t a = __builtin_bit_cast(uint64_t, v), b = __builtin_bit_cast(uint64_t, wrap);
+    const uint32_t lo = (uint32_t)quad_next((int)(uint32_t)a, (int)(uint32_t)b, first);
+    const uint32_t hi = (uint32_t)quad_next((int)(uint32_t)(a >> 32), (int)(uint32_t)(b >> 32), first);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// cells from one velocity column to the next in a column's LDS: the span, four
+// zero cells before and after, an odd multiple of 4
+__host__ __device__ inline int acc_stride(int mx) { return 4 * ((mx + 2) | 1); }
+
+// Bound by FP64 vector instructions: 1.1 to 1.9 ms a remap of the 3.5 million
+// blocks of a 24x24x12 BF16 mixture (its bytes, read and written once, take
+// 0.2 ms), of which 1.5 to 2.4 ms went to 171 vector instructions a block
+// before a face's five cells lay at one address with offsets and the parabola
+// was put in face offsets (fewer roundings, too: the error against 64 bits on
+// 11x9x7 FP64 cells went from 5.0e-15 to 4.6e-15).  A workgroup is one
+// wavefront, so the columns in LDS, 16 acc_stride values of the storage type
+// each, pack a compute unit's 160 KiB without a remainder.
+template <int ST>
+__global__ __launch_bounds__(64) void k_accel_remap(Dev D, AccelParams ap, int k)
+{
+    using St = Storage<ST>;
+    using T = typename St::T;
+    extern __shared__ __align__(16) unsigned char smem[];
+    if (failed(D)) return;
+    const int lane = threadIdx.x;
+    T *s_a = (T *)smem;
+    const int d = ap.order[k];
+    const int e1 = (d == 0) ? 1 : 0, e2 = (d == 2) ? 1 : 2;
+    const int nb1 = D.nblk[e1];
+    const bool last = k == 2;
+    // lane = 4 x velocity column + cell along d; its value in a block
+    const int ld = lane & 3, l1 = (lane >> 2) & 3, l2 = lane >> 4;
+    const bool first = ld == 0;
+    const int mem = (ld << (2 * d)) + (l1 << (2 * e1)) + (l2 << (2 * e2));
+    const uint32_t off = (uint32_t)mem * St::BYTES;
+    // cell j of velocity column c lies at c S + 4 + j: a face's five cells are
+    // one address and offsets; S is an odd multiple of 4, so the quads of a
+    // wavefront fall on different banks
+    const int S = acc_stride(ap.mx);
+    T *col_a = s_a + (lane >> 2) * S + 4;
+    const int64_t nitems = min((int64_t)D.ctl->acc_items[k], D.item_cap);
+    col_a[ld - 4] = (T)0;  // the block before every column
+    for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
+        const Item item = D.items[it];
+        const int32_t pk = __builtin_amdgcn_readfirstlane(item.id);
+        const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane(item.pencil);
+        const int col = pk & 0xfff, lo = (pk >> 12) & 63, hi = (pk >> 18) & 63;
+        const int n = hi - lo + 1;
+        const uint32_t yz = q / (uint32_t)D.n[0], z = yz / (uint32_t)D.n[1];
+        const int64_t ls = D.lstart[cell_index(D, (int)(q - yz * D.n[0]) + H, (int)(yz - z * D.n[1]) + H, (int)z + H)];
+        // lane u: list place and slot of the column's block u
+        const uint32_t ent = lane < n ? (uint32_t)D.rows[item.rowoff + lane] : 0u;
+        const int pos = (int)(ent & ROW_PLACE);
+        const uint32_t slot = lane < n ? (uint32_t)D.lslot[ls + pos] : 0u;
+        const uint32_t code = slot | ((ent & ROW_NEW) ? NEWFLAG : 0u);
+        double row[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) row[j] = ap.maps[ACC_MAP * (int64_t)q + 4 * k + j];
+        const double inv_alpha = 1.0 / row[d];
+        const double sigma = col_sigma(D, row, d, e1, e2, 4 * (col % nb1) + l1, 4 * (col / nb1) + l2);
+        // the column's values, eight blocks' loads in flight (created blocks
+        // read as zero), and the block after it
+        for (int u0 = 0; u0 < n; u0 += 8) {
+            T v[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane((int)code, min(u0 + u, n - 1));
+                v[u] = block_load_raw<ST>(block_rsrc_if<ST>(D.pool, sl, (int32_t)sl >= 0), off);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (u0 + u < n) col_a[4 * (u0 + u) + ld] = v[u];
+        }
+        col_a[4 * n + ld] = (T)0;
+        acc_wave_sync();
+        const int base = 4 * lo, ncell = 4 * n;
+        // average of the column's cell j (relative to base, -4 <= j < ncell + 4)
+        auto a = [&](int j) -> double { return St::widen(col_a[j]); };
+        int jp = 0, fl = 0;
+        double hp = 0.0, ap0 = 0.0;  // the lower faces of the block before: source cell, head, its average
+        for (int b = 0; b <= n; b++) {
+            // lower face of cell base + 4 b + ld: its departure point lies in
+            // source cell j, a fraction xf above the cell's lower edge
+            double xd = ((double)(base + 4 * b + ld) - sigma) * inv_alpha;
+            xd = fmin(fmax(xd, (double)(base - 1)), (double)(base + ncell + 1));
+            const double f = floor(xd);
+            const int j = (int)f - base;
+            const double xf = xd - f;
+            const double a0 = a(j);
+            const double hd = col_head(a(j - 2), a(j - 1), a0, a(j + 1), a(j + 2), xf);
+            // cells outside the span hold zero: flat zero parabolas
+            const double h = (unsigned)j < (unsigned)ncell && xf > 0.0 ? hd : 0.0;
+            if (b > 0) {
+                // new averages of block b - 1: the tail of the first source
+                // cell, the cells covered whole, the head of the last
+                const int j1 = quad_next(jp, j, first);
+                const double h1 = quad_next(hp, h, first);
+                double v = jp == j1 ? h1 - hp : ap0 - hp;
+                if (jp != j1) {
+                    for (int m = jp + 1; m < j1; m++) v += a(m);
+                    v += h1;
+                }
+                const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane((int)slot, b - 1);
+                if constexpr (ST == VL_F64)
+                    block_store(block_rsrc<ST>(D.pool, sl), off, v);
+                else if constexpr (ST == VL_F32)
+                    block_store(block_rsrc<ST>(D.pool, sl), off, (float)v);
+                else
+                    block_store(block_rsrc<ST>(D.pool, sl), off, St::encode(v));
+                if (last) {
+                    const double sv = St::round(v);
+                    const unsigned long long bc = __ballot(sv >= D.sparse_min), bz = __ballot(sv != 0.0);
+                    if (lane == b - 1) fl = (bc ? 1 : 0) | (bz ? 2 : 0);
+                }
+            }
+            jp = j;
+            hp = h;
+            ap0 = a0;
+        }
+        if (last && lane < n) D.litem[ls + pos] = fl | ((ent & ROW_STEP) ? 4 : 0);
+        acc_wave_sync();
+    }
+}
+
+// LDS bound of a velocity mesh (what a workgroup that held a cell's sets and a
+// whole block column would take; both kernels take less), or 0 if the mesh is
+// beyond the kernels' limits
 size_t accel_lds_bytes(const Dev &D, int *ncols, int *hc)
 {
     int nc = 0, mx = 0;
@@ -590,7 +664,10 @@ static AccelParams accel_params(const Dev &D, const double *fields, double *maps
     for (int k = 0; k < 3; k++) ap.order[k] = order[k];
     ap.cur = cur;
     ap.ncols = 0;
-    ap.hc = 0;
+    ap.mx = 0;
+    ap.q0 = 0;
+    for (int j = 0; j < 2; j++)
+        ap.mg[j] = (uint32_t)((((uint64_t)1 << 32) + D.nblk[j] - 1) / D.nblk[j]);  // (1 block: not used)
     return ap;
 }
 
@@ -601,16 +678,46 @@ void launch_accel_maps(const Dev &D, const double *fields, double *maps, int *ba
     hipLaunchKernelGGL(k_accel_factors, dim3((unsigned)((D.nlocal + 255) / 256)), dim3(256), 0, st, D, ap);
 }
 
+template <int ST>
+static void launch_remap(const Dev &D, const AccelParams &ap, int k, hipStream_t st)
+{
+    // one round of workgroups: as many wavefronts as a compute unit's LDS holds
+    // columns for, and its registers wavefronts
+    static const int ncu = [] {
+        int dev = 0, n = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            n = 256;
+        return n;
+    }();
+    const size_t lds = (size_t)16 * acc_stride(ap.mx) * Storage<ST>::BYTES;
+    const int per = (int)std::max<size_t>(1, std::min<size_t>(32, (160 * 1024) / lds));
+    hipLaunchKernelGGL(k_accel_remap<ST>, dim3((unsigned)(ncu * per)), dim3(64), lds, st, D, ap, k);
+}
+
 int launch_accel(const Dev &D, double *maps, const int order[3], int cur, hipStream_t st)
 {
     AccelParams ap = accel_params(D, nullptr, maps, nullptr, 0.0, 0.0, order, cur);
-    const size_t lds = accel_lds_bytes(D, &ap.ncols, &ap.hc);
-    if (lds == 0) return -1;
-    const dim3 g((unsigned)D.nlocal), b(256);
-    switch (D.storage) {
-    case VL_F64: hipLaunchKernelGGL(k_accel<VL_F64>, g, b, lds, st, D, ap); break;
-    case VL_F32: hipLaunchKernelGGL(k_accel<VL_F32>, g, b, lds, st, D, ap); break;
-    default: hipLaunchKernelGGL(k_accel<VL_BF16>, g, b, lds, st, D, ap); break;
+    int hc = 0;
+    if (accel_lds_bytes(D, &ap.ncols, &hc) == 0) return -1;
+    ap.mx = hc / 4;
+    const size_t lds = sizeof(uint32_t) * (size_t)D.W * 2 + sizeof(int) * ((size_t)D.W + 1 + 3 * (size_t)ap.ncols);
+    // A remap has at most one item per block, which the item array holds in a
+    // partition of up to 2^24 blocks; a larger one takes its cells in launches
+    // whose columns are sure to fit.
+    const int64_t tot = D.lcap + D.gcap;
+    const int64_t step = D.item_cap >= tot ? D.nlocal : std::max<int64_t>(1, D.item_cap / ap.ncols);
+    for (ap.q0 = 0; ap.q0 < D.nlocal; ap.q0 += step) {
+        const int64_t ncell = std::min(step, D.nlocal - ap.q0);
+        if (ap.q0 > 0) launch_book(D, BOOK_COLUMNS, st);
+        for (int k = 0; k < 3; k++) {
+            hipLaunchKernelGGL(k_accel_plan, dim3((unsigned)ncell), dim3(256), lds, st, D, ap, k);
+            switch (D.storage) {
+            case VL_F64: launch_remap<VL_F64>(D, ap, k, st); break;
+            case VL_F32: launch_remap<VL_F32>(D, ap, k, st); break;
+            default: launch_remap<VL_BF16>(D, ap, k, st); break;
+            }
+        }
     }
     return 0;
 }

@@ -22,6 +22,11 @@ __global__ void k_book(Dev D, int op)
     }
     if (op == BOOK_GHOST_RESET) return;
     for (int s = 0; s < 3; s++) {
+        c->acc_items[s] = 0;
+        c->acc_rows[s] = 0;
+    }
+    if (op == BOOK_COLUMNS) return;
+    for (int s = 0; s < 3; s++) {
         c->upd_ps[s] = 0;
         c->read_ps[s] = 0;
         c->items[s] = 0;

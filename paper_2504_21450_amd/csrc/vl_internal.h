@@ -66,6 +66,8 @@ struct Ctl {
     unsigned long long face_slots[3], face_list[3];
     // ghost update that is not carried out: sums over the workgroups so far
     unsigned long long acc_slots, acc_list, acc_ticket;
+    // per remap of an acceleration step: block columns and their rows
+    unsigned long long acc_items[3], acc_rows[3];
     // phase-space cells per shear: of the ghost scheme, and those the shear
     // itself writes and reads
     unsigned long long upd_ps[3], read_ps[3], items[3];
@@ -246,7 +248,7 @@ void launch_prune(const Dev &D, int nxt_region, int last_axis, hipStream_t st);
 // velocity map in the given order (ACC_MAP doubles each; *bad set to nonzero
 // if a cell's map cannot be split), then the three remaps of every cell's
 // velocity space; launch_accel returns -1 if the velocity mesh is beyond the
-// kernel's limits (more than ACC_MAX_NBLK blocks along an axis)
+// kernels' limits (more than ACC_MAX_NBLK blocks along an axis)
 constexpr int ACC_MAX_NBLK = 64;
 constexpr int ACC_MAP_DOUBLES = 12;
 void launch_accel_maps(const Dev &D, const double *fields, double *maps, int *bad, double qm, double dt,
@@ -287,6 +289,7 @@ enum {
     BOOK_STEP_A = 2,          // the pruning fills region A
     BOOK_STEP_B = 3,          // region B
     BOOK_FACES = 4,           // flag: ghost allocators to zero as well
+    BOOK_COLUMNS = 8,         // block column counters of an acceleration step to zero
 };
 
 }  // namespace vl
