@@ -920,13 +920,15 @@ int vl_counters(vl_partition *p, uint64_t *out, int32_t n)
     Ctl ctl;
     VL_HIP(hipMemcpyAsync(&ctl, p->D.ctl, sizeof(ctl), hipMemcpyDeviceToHost, p->stream));
     VL_HIP(hipStreamSynchronize(p->stream));
+    auto sum3 = [](const unsigned long long (&a)[3]) { return a[0] + a[1] + a[2]; };
     uint64_t v[32] = {ctl.ring_head, ctl.ring_tail, ctl.ring_limit, ctl.ghost_top + ctl.face_slots[2],
                       ctl.ghost_list_top + ctl.face_list[2],
                       ctl.list_top[0], ctl.list_top[1], ctl.n_items[2], ctl.row_top[2], 0, ctl.err,
                       ctl.upd_ps[0], ctl.upd_ps[1], ctl.upd_ps[2], ctl.read_ps[0], ctl.read_ps[1],
                       ctl.read_ps[2], ctl.items[0], ctl.items[1], ctl.items[2], (uint64_t)p->cur,
-                      ctl.cum_upd, ctl.cum_read, ctl.run_upd[0], ctl.run_upd[1], ctl.run_upd[2],
-                      ctl.run_read[0], ctl.run_read[1], ctl.run_read[2], ctl.cum_run_upd, ctl.cum_run_read};
+                      ctl.cum_upd + sum3(ctl.upd_ps), ctl.cum_read + sum3(ctl.read_ps), ctl.run_upd[0], ctl.run_upd[1], ctl.run_upd[2],
+                      ctl.run_read[0], ctl.run_read[1], ctl.run_read[2],
+                      ctl.cum_run_upd + sum3(ctl.run_upd), ctl.cum_run_read + sum3(ctl.run_read)};
     for (int i = 0; i < n; i++) out[i] = v[i];
     return VL_OK;
 }

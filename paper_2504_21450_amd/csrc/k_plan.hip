@@ -770,10 +770,6 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
         atomicAdd(&D.ctl->items[pp.sidx], mult * (unsigned long long)n);
         atomicAdd(&D.ctl->run_upd[pp.sidx], (unsigned long long)(u * BLK));
         atomicAdd(&D.ctl->run_read[pp.sidx], (unsigned long long)(o * BLK));
-        atomicAdd(&D.ctl->cum_upd, mult * (unsigned long long)(u * BLK));
-        atomicAdd(&D.ctl->cum_read, mult * (unsigned long long)(r * BLK));
-        atomicAdd(&D.ctl->cum_run_upd, (unsigned long long)(u * BLK));
-        atomicAdd(&D.ctl->cum_run_read, (unsigned long long)(o * BLK));
     }
 }
 

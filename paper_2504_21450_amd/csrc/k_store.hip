@@ -26,6 +26,11 @@ __global__ void k_book(Dev D, int op)
         c->acc_rows[s] = 0;
     }
     if (op == BOOK_COLUMNS) return;
+    // the last translation step's cells into the running totals
+    c->cum_upd += c->upd_ps[0] + c->upd_ps[1] + c->upd_ps[2];
+    c->cum_read += c->read_ps[0] + c->read_ps[1] + c->read_ps[2];
+    c->cum_run_upd += c->run_upd[0] + c->run_upd[1] + c->run_upd[2];
+    c->cum_run_read += c->run_read[0] + c->run_read[1] + c->run_read[2];
     for (int s = 0; s < 3; s++) {
         c->upd_ps[s] = 0;
         c->read_ps[s] = 0;
