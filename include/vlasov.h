@@ -166,8 +166,8 @@ int vl_load_values(vl_partition *p, int64_t first_block, int64_t nblocks, const 
  * With gt_level 3 and at least 3 cells along each axis no copy is made: every
  * ghost line would be given the values of the local line that it is an image
  * of, so the step's shears run the local lines alone and read their ends
- * through the period, and this call only checks that the ghost lists and
- * blocks fit their capacities.
+ * through the period (ghost blocks then take no room: ghost_block_capacity
+ * bounds copied ones).
  * VL_ERR_ARG if desc.edges is set (boundary cells need their sources). */
 int vl_fill_ghosts(vl_partition *p);
 

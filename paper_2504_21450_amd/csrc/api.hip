@@ -261,7 +261,7 @@ void update_box(const vl_partition *p, int mode, int s, int lo[3], int hi[3])
 }
 
 // Whether the partition's steps read the periodic images of its cells in place
-// (WRAP_ON, planner): its ghost cells are its own images (no neighbours given,
+// (wrap, planner and shear): its ghost cells are its own images (no neighbours given,
 // no simulation edge) and every ghost layer is recomputed (GT level 3; fewer
 // layers leave the outer ones at their old values, which differ from their
 // images').  Lines of fewer than 3 cells meet themselves within the stencil
@@ -296,13 +296,13 @@ void enqueue_translate(vl_partition *p, double dt, int mode, double *ledger3, hi
     const bool ledger = p->lay.lg_cap > 0;
     LedgerRot rot = p->rot;
     p->loadable = false;
-    const int wrap = !wraps(p) ? WRAP_OFF : mode == VL_PER_SWEEP ? WRAP_FACES : WRAP_ON;
-    launch_book(D, (nxt == 0 ? BOOK_STEP_A : BOOK_STEP_B) | (wrap == WRAP_FACES ? BOOK_FACES : 0), st);
+    const bool wrap = wraps(p);
+    launch_book(D, nxt == 0 ? BOOK_STEP_A : BOOK_STEP_B, st);
     for (int s = 0; s < 3; s++) {
         const int d = p->desc.order[s];
         int lo[3], hi[3];
         update_box(p, mode, s, lo, hi);
-        if (mode == VL_PER_SWEEP && wrap == WRAP_OFF) {
+        if (mode == VL_PER_SWEEP && !wrap) {
             int flo[3], fhi[3];
             for (int e = 0; e < 3; e++) {
                 flo[e] = H;
@@ -327,7 +327,7 @@ void enqueue_translate(vl_partition *p, double dt, int mode, double *ledger3, hi
         }
         {
             ProfScope ps(p, K_PLAN);
-            if (ledger && wrap == WRAP_OFF) launch_zero_i32(lg.nw.kcnt, p->lay.pen_cap, st);
+            if (ledger && !wrap) launch_zero_i32(lg.nw.kcnt, p->lay.pen_cap, st);
             launch_plan(D, d, s, lo, hi, dt, p->cur, lg, wrap, st);
         }
         {
@@ -347,11 +347,7 @@ void enqueue_fill(vl_partition *p, hipStream_t st)
 {
     const Dev &D = p->D;
     int lo[3] = {0, 0, 0}, hi[3] = {D.P[0], D.P[1], D.P[2]};
-    if (wraps(p)) {  // the steps read the images in place
-        ProfScope ps(p, K_FILL);
-        launch_ghost_count(D, st);
-        return;
-    }
+    if (wraps(p)) return;  // the steps read the images in place: nothing to copy
     launch_book(D, BOOK_GHOST_RESET, st);
     ProfScope ps(p, K_FILL);
     if (p->has_src)  // the sources of the last vl_fill_ghosts_from
@@ -921,8 +917,7 @@ int vl_counters(vl_partition *p, uint64_t *out, int32_t n)
     VL_HIP(hipMemcpyAsync(&ctl, p->D.ctl, sizeof(ctl), hipMemcpyDeviceToHost, p->stream));
     VL_HIP(hipStreamSynchronize(p->stream));
     auto sum3 = [](const unsigned long long (&a)[3]) { return a[0] + a[1] + a[2]; };
-    uint64_t v[32] = {ctl.ring_head, ctl.ring_tail, ctl.ring_limit, ctl.ghost_top + ctl.face_slots[2],
-                      ctl.ghost_list_top + ctl.face_list[2],
+    uint64_t v[32] = {ctl.ring_head, ctl.ring_tail, ctl.ring_limit, ctl.ghost_top, ctl.ghost_list_top,
                       ctl.list_top[0], ctl.list_top[1], ctl.n_items[2], ctl.row_top[2], 0, ctl.err,
                       ctl.upd_ps[0], ctl.upd_ps[1], ctl.upd_ps[2], ctl.read_ps[0], ctl.read_ps[1],
                       ctl.read_ps[2], ctl.items[0], ctl.items[1], ctl.items[2], (uint64_t)p->cur,

@@ -21,8 +21,8 @@
 // In a periodic partition (template parameter WR) only the local pencils are
 // planned: a pencil's ghost cells are its own first and last cells seen through
 // the period, so their presence bits are copied from those cells' bits, no list
-// is read for them and the row holds the local cells alone; every count of the
-// ghost scheme takes the pencil times its images in the scheme's box.
+// is read for them and the row holds the local cells alone; the statistics of
+// the ghost scheme count the pencil with its images in the scheme's box.
 // (Ghost lines give the values of local lines again and outnumber them in a
 // small box: of the first shear's updates they are 64 % on 16x16x8 cells, 14 %
 // on 64x64x32.  A step with moments, copied ghost lines -> local lines alone:
@@ -46,7 +46,6 @@ struct PlanParams {
     int R;               // chunk capacity (block ids per chunk)
     int cur;             // local list region in use
     int kstride;         // pencil key of (t1, t2): t1 + kstride t2
-    int faces;           // count the refresh of the ghost faces along d
     double dt;
     LedgerIO lg;
 };
@@ -240,9 +239,8 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     const int U = block_scan_excl(s_rank, W, s_tmp);
     // the pencil's items: item first + r for the block of union rank r
     if (tid == 0) {
-        const unsigned long long ib = U > 0 ? atomicAdd(&D.ctl->n_run[pp.sidx], (unsigned long long)U) : 0ull;
-        const unsigned long long vi = U > 0 ? atomicAdd(&D.ctl->n_items[pp.sidx], mult * U) : 0ull;
-        if ((int64_t)(vi + mult * U) > D.item_cap) atomicOr(&D.ctl->err, (unsigned long long)E_ITEMS);
+        const unsigned long long ib = U > 0 ? atomicAdd(&D.ctl->n_items[pp.sidx], (unsigned long long)U) : 0ull;
+        if ((int64_t)(ib + U) > D.item_cap) atomicOr(&D.ctl->err, (unsigned long long)E_ITEMS);
         s_ibp = (long long)ib;
         if (p < D.pen_cap) {
             D.pen_first[p] = (int64_t)ib;
@@ -269,25 +267,6 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                         }
                 }
             }
-        }
-    }
-    if (WR && pp.faces && tid < 64) {  // the ghost faces along d that the scheme would refresh
-        unsigned long long slots = 0, list = 0;
-        for (int i = i0 + tid; i < i1; i += 64) {
-            const unsigned long long m = images(i, i1 - i0, 0, L) - 1;
-            slots += m * (unsigned long long)s_cnt[i];
-            list += m * (unsigned long long)(s_cnt[i] + s_cnt[i] / 4 + 32);
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            slots += __shfl_xor(slots, o);
-            list += __shfl_xor(list, o);
-        }
-        if (tid == 0) {
-            const unsigned long long a = atomicAdd(&D.ctl->face_slots[pp.sidx], slots) + slots;
-            const unsigned long long b = atomicAdd(&D.ctl->face_list[pp.sidx], list) + list;
-            const unsigned long long err = ((int64_t)a > D.gcap ? (unsigned long long)E_GHOST_SLOTS : 0ull) |
-                                           ((int64_t)b > D.reg_cap[2] ? (unsigned long long)E_GHOST_LIST : 0ull);
-            if (err) atomicOr(&D.ctl->err, err);
         }
     }
     __syncthreads();
@@ -429,7 +408,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                     s_pres[k * WL + w] = pn;
                     s_newb[k * WL + w] = G[w];
                     active |= (pn & um[w]) != 0u;
-                    rowlen += popc(pn);
+                    rowlen += popc(WR ? pn & um[w] : pn);  // (WR: the line's own cells)
                     nnew += popc(G[w]);
                     upd += popc(pn & um[w]);
                     rd += popc(P[w]);
@@ -455,7 +434,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 for (int w = 0; w < MAXWL; w++) {
                     if (w < WL) {
                         s_cum[k * WL + w] = active ? (uint8_t)run : (uint8_t)255;
-                        // (WR: rows hold no left ghosts; the right ones' places stay unused)
+                        // (WR: no ghosts before the line; those after it precede none of its cells)
                         run += popc((P[w] | G[w]) & (WR && w == 0 ? ~7u : ~0u));
                     }
                 }
@@ -480,11 +459,6 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             if (have + req <= s_cap[i]) continue;
             const int ncap = (have + req) + (have + req) / 4 + 32;  // the slack of a fresh list
             const int reg = local_pencil ? pp.cur : 2;
-            if (WR && mult > 1) {  // the images' lists in the ghost region
-                const unsigned long long g = (mult - 1) * (unsigned long long)ncap;
-                if ((int64_t)(atomicAdd(&D.ctl->ghost_list_top, g) + g) > D.reg_cap[2])
-                    atomicOr(&D.ctl->err, (unsigned long long)E_LIST);
-            }
             unsigned long long *top = local_pencil ? &D.ctl->list_top[pp.cur] : &D.ctl->ghost_list_top;
             const unsigned long long nb0 = atomicAdd(top, (unsigned long long)ncap);
             if ((int64_t)(nb0 + ncap) > D.reg_cap[reg]) {
@@ -518,11 +492,10 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             s_ro[rn] = nrow;
             s_np[rn] = nnew;
             unsigned long long err = 0;
-            // (WR: the images' rows are counted; only the pencil's are written)
-            unsigned long long rb = atomicAdd(&D.ctl->row_top[pp.sidx], mult * (unsigned long long)nrow);
+            unsigned long long rb = atomicAdd(&D.ctl->row_top[pp.sidx], (unsigned long long)nrow);
             unsigned long long nb = 0;
             unsigned long long ok = 1;
-            if ((int64_t)(rb + mult * nrow) > D.row_cap) {
+            if ((int64_t)(rb + nrow) > D.row_cap) {
                 err |= E_ROWS;
                 ok = 0;
             }
@@ -532,10 +505,6 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                     if (nb + nnew > D.ctl->ring_limit) {
                         err |= E_RING;
                         ok |= 2;  // allocation failed: new blocks go to the scratch slot
-                    }
-                    if (WR && mult > 1) {  // the images' new blocks among the ghost slots
-                        const unsigned long long g = (mult - 1) * (unsigned long long)nnew;
-                        if ((int64_t)(atomicAdd(&D.ctl->ghost_top, g) + g) > D.gcap) err |= E_GHOST_SLOTS;
                     }
                 } else {
                     nb = atomicAdd(&D.ctl->ghost_top, (unsigned long long)nnew);
@@ -795,10 +764,9 @@ void launch_zero_i32(int32_t *p, int64_t n, hipStream_t st)
 }
 
 void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, int cur,
-                 const LedgerIO &lg, int wrap, hipStream_t st)
+                 const LedgerIO &lg, bool wrap, hipStream_t st)
 {
     PlanParams pp;
-    pp.faces = wrap == WRAP_FACES;
     pp.cur = cur;
     pp.lg = lg;
     pp.d = d;
@@ -823,7 +791,7 @@ void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3]
     if (R < 64) R = 64;
     pp.R = R;
     size_t lds = plan_lds_bytes(D.W, R, pp.WL, pp.L);
-    if (wrap != WRAP_OFF) {
+    if (wrap) {
         const int64_t np = (int64_t)D.n[pp.e1] * D.n[pp.e2];
         hipLaunchKernelGGL(k_plan<true>, dim3((unsigned)np), dim3(PNT), lds, st, D, pp);
         return;

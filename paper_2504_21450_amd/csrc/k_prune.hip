@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void k_prune(Dev D, int nxt, int last_axis, do
     const int tc = H + (last_axis == 0 ? x : last_axis == 1 ? y : z);
     const uint32_t *fw = D.masks + (tc >> 5);
     const uint32_t fbit = 1u << (tc & 31);
-    const uint64_t nitems = (uint64_t)min((int64_t)D.ctl->n_run[2], D.item_cap);
+    const uint64_t nitems = (uint64_t)min((int64_t)D.ctl->n_items[2], D.item_cap);
 
     for (int w = tid; w < W; w += 256) {
         s_old[w] = 0u;

@@ -16,11 +16,11 @@ namespace vl {
 __global__ void k_book(Dev D, int op)
 {
     Ctl *c = D.ctl;
-    if (op == BOOK_GHOST_RESET || (op & BOOK_FACES)) {
+    if (op == BOOK_GHOST_RESET) {
         c->ghost_top = 0;
         c->ghost_list_top = 0;
+        return;
     }
-    if (op == BOOK_GHOST_RESET) return;
     for (int s = 0; s < 3; s++) {
         c->acc_items[s] = 0;
         c->acc_rows[s] = 0;
@@ -39,12 +39,9 @@ __global__ void k_book(Dev D, int op)
         c->run_read[s] = 0;
         c->n_items[s] = 0;
         c->row_top[s] = 0;
-        c->n_run[s] = 0;
-        c->face_slots[s] = 0;
-        c->face_list[s] = 0;
     }
     c->ring_limit = c->ring_tail;
-    c->list_top[(op & 3) == BOOK_STEP_A ? 0 : 1] = 0;
+    c->list_top[op == BOOK_STEP_A ? 0 : 1] = 0;
 }
 
 void launch_book(const Dev &D, int op, hipStream_t st)
@@ -201,58 +198,6 @@ __global__ __launch_bounds__(256) void k_fill(Dev D, SrcTable src, int lo0, int 
                 pool[(gslot0 + g + k) * WPB + lane] = spool[(int64_t)__builtin_amdgcn_readlane(mys, k) * WPB + lane];
         }
     }
-}
-
-// The ghost update of a periodic partition whose steps read the images in
-// place: no list and no value is copied; what is left of it is the room that
-// the ghost lists and blocks of the scheme take (each local cell's, times its
-// images in the padded box beyond itself), which must fit as ever.  The last
-// workgroup to finish writes the totals.
-__global__ __launch_bounds__(256) void k_ghost_count(Dev D)
-{
-    __shared__ unsigned long long s_sum[4][2];
-    if (failed(D)) return;  // errors of earlier kernels: the same for every workgroup
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    unsigned long long slots = 0, list = 0;
-    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < D.nlocal; q += (int64_t)gridDim.x * 256) {
-        const int x = (int)(q % D.n[0]) + H, y = (int)((q / D.n[0]) % D.n[1]) + H,
-                  z = (int)(q / ((int64_t)D.n[0] * D.n[1])) + H;
-        const int cnt = D.lcount[cell_index(D, x, y, z)];
-        const unsigned long long m = (unsigned long long)images(x, D.n[0], 0, D.P[0]) * images(y, D.n[1], 0, D.P[1]) *
-                                         images(z, D.n[2], 0, D.P[2]) - 1ull;
-        slots += m * (unsigned long long)cnt;
-        list += m * (unsigned long long)(cnt + cnt / 4 + 32);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        slots += __shfl_xor(slots, o);
-        list += __shfl_xor(list, o);
-    }
-    if (lane == 0) {
-        s_sum[wv][0] = slots;
-        s_sum[wv][1] = list;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    Ctl *c = D.ctl;
-    atomicAdd(&c->acc_slots, s_sum[0][0] + s_sum[1][0] + s_sum[2][0] + s_sum[3][0]);
-    atomicAdd(&c->acc_list, s_sum[0][1] + s_sum[1][1] + s_sum[2][1] + s_sum[3][1]);
-    __threadfence();
-    if (atomicAdd(&c->acc_ticket, 1ull) + 1ull != gridDim.x) return;
-    __threadfence();
-    slots = atomicExch(&c->acc_slots, 0ull);
-    list = atomicExch(&c->acc_list, 0ull);
-    c->acc_ticket = 0ull;
-    c->ghost_top = slots;
-    c->ghost_list_top = list;
-    const unsigned long long err = ((int64_t)slots > D.gcap ? (unsigned long long)E_GHOST_SLOTS : 0ull) |
-                                   ((int64_t)list > D.reg_cap[2] ? (unsigned long long)E_GHOST_LIST : 0ull);
-    if (err) atomicOr(&c->err, err);
-}
-
-void launch_ghost_count(const Dev &D, hipStream_t st)
-{
-    const int64_t g = std::min<int64_t>((D.nlocal + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_ghost_count, dim3((unsigned)g), dim3(256), 0, st, D);
 }
 
 SrcPart self_source(const Dev &D)

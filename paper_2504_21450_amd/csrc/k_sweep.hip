@@ -629,7 +629,7 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
     __shared__ uint32_t s_seg[4][64 * NM / 7 + 2];  // segments of the item: first cell | end << 16
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int d = sp.d, L = sp.L;
-    const int64_t nitems = min((int64_t)D.ctl->n_run[sp.sidx], D.item_cap);
+    const int64_t nitems = min((int64_t)D.ctl->n_items[sp.sidx], D.item_cap);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     uint32_t *srow = s_tab[wv] + WIN0;
     uint32_t *sseg = s_seg[wv];
@@ -892,7 +892,7 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
     const int wv = threadIdx.x >> 6;
     const int d = sp.d, L = sp.L, WL = sp.WL;
     const int ld = (d == 0) ? (lane & 3) : (d == 1) ? ((lane >> 2) & 3) : (lane >> 4);
-    const int64_t nitems = min((int64_t)D.ctl->n_run[sp.sidx], D.item_cap);
+    const int64_t nitems = min((int64_t)D.ctl->n_items[sp.sidx], D.item_cap);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     int64_t it = (int64_t)blockIdx.x * 4 + wv;
     if (it >= nitems) return;
@@ -1034,10 +1034,10 @@ static void launch_st(const Dev &D, const SweepParams &sp, int v, hipStream_t st
 int sweep_variants() { return NVARIANTS; }
 
 void launch_sweep(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, bool last,
-                  const LedgerIO &lg, int wrap, hipStream_t st)
+                  const LedgerIO &lg, bool wrap, hipStream_t st)
 {
     SweepParams sp;
-    sp.wrap = wrap == WRAP_OFF ? 0 : D.n[d];
+    sp.wrap = wrap ? D.n[d] : 0;
     sp.lg_old = lg.old.res;
     sp.lg_new = lg.nw.res;
     sp.lg_src = lg.src;

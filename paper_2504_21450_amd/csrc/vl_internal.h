@@ -67,19 +67,9 @@ struct Ctl {
     VL_OWN_LINE ghost_top;
     VL_OWN_LINE ghost_list_top;
     VL_OWN_LINE list_top[2];
-    // per shear of the step: items and rows of the ghost scheme, and the items
-    // the shear runs (fewer where ghost lines are images of local ones)
+    // per shear of the step: items and rows
     VL_OWN_LINE n_items[3];
     VL_OWN_LINE row_top[3];
-    VL_OWN_LINE n_run[3];
-    // per shear: ghost slots and list entries of a face refresh that is not
-    // carried out (per-sweep steps of a periodic partition)
-    VL_OWN_LINE face_slots[3];
-    VL_OWN_LINE face_list[3];
-    // ghost update that is not carried out: sums over the workgroups so far
-    VL_OWN_LINE acc_slots;
-    VL_OWN_LINE acc_list;
-    VL_OWN_LINE acc_ticket;
     // per remap of an acceleration step: block columns and their rows
     VL_OWN_LINE acc_items[3];
     VL_OWN_LINE acc_rows[3];
@@ -244,17 +234,13 @@ SrcPart self_source(const Dev &D);
 // whose shears recompute every ghost layer that later shears read gives each
 // ghost line exactly the values of its local image.  wrap: plan and run the
 // local lines alone, their ends reading the line's own cells through the
-// period; the scheme's counts (updated cells, items, ghost slots and lists)
-// are kept by multiplying each line by its images in the scheme's box
-// [lo, hi).  faces: the scheme refreshes the ghost faces along d before this
-// shear (per-sweep mode), counted as well.
-enum { WRAP_OFF = 0, WRAP_ON = 1, WRAP_FACES = 2 };
-void launch_ghost_count(const Dev &D, hipStream_t st);
+// period; the scheme's statistics (updated and read cells, items) count each
+// line with its images in the scheme's box [lo, hi).
 void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, int cur,
-                 const LedgerIO &lg, int wrap, hipStream_t st);
+                 const LedgerIO &lg, bool wrap, hipStream_t st);
 int sweep_variants();
 void launch_sweep(const Dev &D, int d, int sidx, const int lo[3], const int hi[3], double dt, bool last,
-                  const LedgerIO &lg, int wrap, hipStream_t st);
+                  const LedgerIO &lg, bool wrap, hipStream_t st);
 // n int32 zeros at p (a kernel, so that graph captures hold no memset node)
 void launch_zero_i32(int32_t *p, int64_t n, hipStream_t st);
 // FP64 sum of the terminal residuals of the shear's local pencils into *out:
@@ -307,8 +293,7 @@ enum {
     // allocator of the list region that the pruning fills to zero
     BOOK_STEP_A = 2,          // the pruning fills region A
     BOOK_STEP_B = 3,          // region B
-    BOOK_FACES = 4,           // flag: ghost allocators to zero as well
-    BOOK_COLUMNS = 8,         // block column counters of an acceleration step to zero
+    BOOK_COLUMNS = 4,         // block column counters of an acceleration step to zero
 };
 
 }  // namespace vl
