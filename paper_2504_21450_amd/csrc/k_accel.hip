@@ -386,7 +386,7 @@ __global__ __launch_bounds__(256) void k_accel_plan(Dev D, AccelParams ap, int k
         if (sp >= 0) {
             Item it;
             it.id = pack_column(col, sp & 0xffff, sp >> 16);
-            it.pencil = (int32_t)q;
+            it.key = (int32_t)q;
             it.rowoff = rb + run_row;
             D.items[(int64_t)s_base[0] + run_item] = it;
             run_item++;
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(64) void k_accel_remap(Dev D, AccelParams ap, int k
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const Item item = D.items[it];
         const int32_t pk = __builtin_amdgcn_readfirstlane(item.id);
-        const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane(item.pencil);
+        const uint32_t q = (uint32_t)__builtin_amdgcn_readfirstlane(item.key);
         const int col = pk & 0xfff, lo = (pk >> 12) & 63, hi = (pk >> 18) & 63;
         const int n = hi - lo + 1;
         const uint32_t yz = q / (uint32_t)D.n[0], z = yz / (uint32_t)D.n[1];

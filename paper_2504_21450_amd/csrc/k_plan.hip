@@ -535,7 +535,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 if (it < D.item_cap) {
                     Item item;
                     item.id = s_id[k];
-                    item.pencil = p;
+                    item.key = block_coord(D, pp.d, s_id[k]);
                     item.rowoff = 0;
                     D.items[it] = item;
                     for (int w = 0; w < D.wlmax; w++) D.masks[it * D.wlmax + w] = 0u;
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             if (it < D.item_cap) {
                 Item item;
                 item.id = s_id[k];
-                item.pencil = p;
+                item.key = block_coord(D, pp.d, s_id[k]);
                 item.rowoff = rows_ok ? rowoff : 0;
                 D.items[it] = item;
                 for (int w = 0; w < D.wlmax; w++)

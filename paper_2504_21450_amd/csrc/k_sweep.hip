@@ -106,12 +106,6 @@ constexpr int TABLE = WIN0 + 64 * NM + 72;
 
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// sum over the wavefront's 64 lanes, the same pairing every time
-__device__ __forceinline__ double wave_sum64(double v)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
 
 __device__ __forceinline__ double uniform_f64(double v)
 {
@@ -150,7 +144,7 @@ __device__ __forceinline__ void leave_residual(const Dev &D, const SweepParams &
                                                double carry, double start_sum)
 {
     if constexpr (ST != VL_F64) {
-        const double s = wave_sum64(carry);
+        const double s = wave_sum_f64(carry);
         if (lane == 0) {
             if (it < sp.lg_cap) sp.lg_new[it] = s;
             D.resid[it] = s - start_sum;
@@ -200,6 +194,18 @@ __device__ __forceinline__ C limited_slope2(C dl, C dr, C d2)
         const C m = fmax((C)0, fmin(fmin(fabs(d2), s4 * dl), s4 * dr));
         return copysign(m, d2);
     }
+}
+
+// the face between a cell of average a0 and the next, d above it, with twice
+// their limited slopes s0 and s1 (CW84 eq. 1.6; the fused operations written
+// out, as a march's start and its iterations have to agree to the last bit)
+__device__ __forceinline__ float face_value(float a0, float d, float s1, float s0)
+{
+    return fmaf(-(s1 - s0), (float)(0.5 / 6.0), fmaf(0.5f, d, a0));
+}
+__device__ __forceinline__ double face_value(double a0, double d, double s1, double s0)
+{
+    return fma(-(s1 - s0), 0.5 / 6.0, fma(0.5, d, a0));
 }
 
 // the monotonicity limiter's face offset x given the other side's offset y
@@ -397,27 +403,34 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
         return block_load<ST>(block_rsrc_if<ST>(D.pool, sl, (int32_t)sl >= 0), lane_off);
     };
 
-    C a1 = 0, a2 = 0;
-    double a3d = 0.0;
-    C da_prev = 0;
-    C face_prev = 0;
-    double Fc_prev = 0.0, Ff_prev = 0.0;
+    // The front starts at cell tb + 2: with zeros before cell tb, the fluxes
+    // of the cells before it are zero, and the state at tb + 2 is the slope of
+    // cell tb and the face below it.  It ends with the cell te - 1, whose
+    // iteration writes the segment's last cell (a check per iteration: runs of
+    // nine cells, usual on the lines of a mixture's hot blobs, take 10
+    // iterations instead of 12 to 16 in whole groups from tb).
+    const int t_first = tb + 2;
     C q[PFV];
     // raw slots of the cells t0 .. t0+PFV-1 (fetched by the previous group or
     // the prologue), of the three cells before them, and of the cells this
     // group fetches
     uint32_t prv[PFV], bef[3], cur[PFV];
     // lane j of the window holds cell w0 - WIN0 + j
-    uint32_t win = srow[tb - WIN0 + lane];
+    uint32_t win = srow[t_first - WIN0 + lane];
+#pragma unroll
+    for (int i = 0; i < 3; i++) bef[i] = (uint32_t)__builtin_amdgcn_readlane((int)win, WIN0 - 3 + i);
+    C a2 = fetch_raw(bef[1]), a1 = fetch_raw(bef[2]);  // cells t-2, t-1
 #pragma unroll
     for (int u = 0; u < PFV; u++) {
         prv[u] = (uint32_t)__builtin_amdgcn_readlane((int)win, WIN0 + u);
         q[u] = fetch_raw(prv[u]);
     }
-#pragma unroll
-    for (int i = 0; i < 3; i++) bef[i] = (uint32_t)__builtin_amdgcn_readlane((int)win, WIN0 - 3 + i);
-    for (int w0 = tb; w0 < te; w0 += WSTEP) {
-        if (w0 != tb) win = srow[w0 - WIN0 + lane];
+    double a3d = 0.0;
+    C da_prev = limited_slope2(a2, a1 - a2, a1);
+    C face_prev = face_value((C)0, a2, da_prev, (C)0);
+    double Fc_prev = 0.0, Ff_prev = 0.0;
+    for (int w0 = t_first; w0 < te; w0 += WSTEP) {
+        if (w0 != t_first) win = srow[w0 - WIN0 + lane];
         // the window's cells that this march writes: local ones before te - 3
         // (those from there on belong to the next segment's march)
         const int jlo = max(0, H + WIN0 - w0), jhi = min(L - H, te - 3) + WIN0 - w0;
@@ -431,7 +444,7 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
                 q[u] = fetch_raw(cur[u]);
                 const C dl = a1 - a2, dr = a - a1;
                 const C da = limited_slope2(dl, dr, a - a2);
-                const C face = a2 + (C)0.5 * (a1 - a2) - (da - da_prev) * (C)(0.5 / 6.0);
+                const C face = face_value(a2, a1 - a2, da, da_prev);
                 const C ai = a2;
                 const C dL = ai - face_prev, dR = face - ai;
                 const double dLp = (double)limited_offset(dL, dR), dRp = (double)limited_offset(dR, dL);
@@ -564,7 +577,7 @@ __device__ __forceinline__ uint64_t down(const uint64_t (&v)[NM], int w, int s)
 // an item's place in the row table, presence mask and old ledger item
 template <int NM>
 struct ItemMeta {
-    int32_t id, src;
+    int32_t bd, src;
     int64_t rowoff;
     uint64_t m[NM];
 };
@@ -574,8 +587,8 @@ __device__ __forceinline__ ItemMeta<NM> load_meta(const Dev &D, const SweepParam
 {
     ItemMeta<NM> M;
     const int32_t *ip = (const int32_t *)(D.items + it);
-    static_assert(sizeof(Item) == 16 && offsetof(Item, id) == 0 && offsetof(Item, rowoff) == 8, "item layout");
-    M.id = scalar_load(ip, 0);
+    static_assert(sizeof(Item) == 16 && offsetof(Item, key) == 4 && offsetof(Item, rowoff) == 8, "item layout");
+    M.bd = scalar_load(ip, 1);
     M.rowoff = scalar_load((const int64_t *)ip, 1);
     const uint32_t *mw = D.masks + it * D.wlmax;
 #pragma unroll
@@ -689,14 +702,8 @@ __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)
         load_row<NM>(D, sp, N, lane, rv);
         const double next_sum = take_residual<ST>(sp, N.src);
 
-        // the block's coordinate along d (the mesh extents passed through an
-        // empty asm, so the divisions' reciprocals are formed per item, not
-        // kept in registers across items) and the lane's velocity cell in it
-        int nb0 = D.nblk[0], nb1 = D.nblk[1];
-        __asm__ volatile("" : "+s"(nb0), "+s"(nb1));
-        const int bd = (d == 0) ? M.id % nb0 : (d == 1) ? (M.id / nb0) % nb1 : M.id / (nb0 * nb1);
         const int ld = (d == 0) ? (lane & 3) : (d == 1) ? ((lane >> 2) & 3) : (lane >> 4);
-        const double c = courant(D, d, 4 * bd + ld, sp.dt);
+        const double c = courant(D, d, 4 * M.bd + ld, sp.dt);
         const unsigned long long npos = __ballot(c > 0.0), nneg = __ballot(c < 0.0);
         // March each segment of cells holding the block: from its first such
         // cell to three past its last (where the last one is written).  Before
@@ -918,9 +925,7 @@ __device__ __forceinline__ void sweep_stream(const Dev &D, const SweepParams &sp
     }
     for (; it < nitems; it += nwaves) {
         const int64_t nit = it + nwaves;
-        const int32_t id = D.items[it].id;
-        const int bd = block_coord(D, d, id);
-        const double c = courant(D, d, 4 * bd + ld, sp.dt);
+        const double c = courant(D, d, 4 * D.items[it].key + ld, sp.dt);
         const unsigned long long npos = __ballot(c > 0.0), nneg = __ballot(c < 0.0);
         int32_t src = -1;
         if constexpr (ST != VL_F64)
@@ -1076,7 +1081,7 @@ __global__ __launch_bounds__(256) void k_ledger_pencils(Dev D, int e1, int e2, i
         const int64_t cnt = min((int64_t)D.pen_cnt[p], max((int64_t)0, D.item_cap - first));
         for (int64_t k = lane; k < cnt; k += 64) acc += D.resid[first + k];
     }
-    acc = wave_sum64(acc);
+    acc = wave_sum_f64(acc);
     if (lane == 0) pen_sum[p] = acc;
 }
 

@@ -91,7 +91,7 @@ struct Ctl {
 
 struct Item {
     int32_t id;       // velocity block id
-    int32_t pencil;   // pencil index within the shear
+    int32_t key;      // shear: the block's coordinate along the axis; acceleration: local cell
     int64_t rowoff;   // first row entry
 };
 

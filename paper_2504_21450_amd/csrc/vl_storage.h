@@ -112,6 +112,39 @@ struct Storage<VL_BF16> {
 
 inline int storage_bytes(int st) { return st == VL_F64 ? 8 : st == VL_F32 ? 4 : 2; }
 
+// Sum over the wavefront's 64 lanes, the pairs 32, 16, .., 1 lanes apart, in
+// every lane, without LDS: the halves and the odd rows of 16 swapped, then
+// rotations within the rows (once lanes 8 apart hold the same value, the lane 4
+// further on in the row holds what the lane 4 apart does, and so on).
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    auto join = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo); };
+    {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const auto l = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+        v = join(l[0], h[0]) + join(l[1], h[1]);
+    }
+    {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const auto l = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+        v = join(l[0], h[0]) + join(l[1], h[1]);
+    }
+#define VL_ROW_ADD(ctrl)                                                                                          \
+    do {                                                                                                          \
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);                                                       \
+        v += join((uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, ctrl, 0xf, 0xf, true),                     \
+                  (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), ctrl, 0xf, 0xf, true));            \
+    } while (0)
+    VL_ROW_ADD(0x128);  // row_ror:8
+    VL_ROW_ADD(0x124);  // row_ror:4
+    VL_ROW_ADD(0x122);  // row_ror:2
+    VL_ROW_ADD(0x121);  // row_ror:1
+#undef VL_ROW_ADD
+    return v;
+}
+
 // One block (64 values of one cell) of the pool as a buffer resource: the
 // block's address is formed in scalar registers and each lane's value is at
 // byte offset lane * bytes, so no vector instruction computes addresses.
