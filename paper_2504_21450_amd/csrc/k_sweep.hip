@@ -436,57 +436,69 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
         const int jlo = max(0, H + WIN0 - w0), jhi = min(L - H, te - 3) + WIN0 - w0;
         unsigned long long wm = __ballot(win != ABSENT && lane >= jlo && lane < jhi) >> (WIN0 - 3);
         const int iend = min(WSTEP, te - w0);
-        for (int i0 = 0; i0 < iend; i0 += PFV) {
+        // one iteration, cell t = w0 + i0 + u; slot3 is the slot of cell t - 3
+        auto iteration = [&](C a, uint32_t slot3, bool write, int t) {
+            const C dl = a1 - a2, dr = a - a1;
+            const C da = limited_slope2(dl, dr, a - a2);
+            const C face = face_value(a2, a1 - a2, da, da_prev);
+            const C ai = a2;
+            const C dL = ai - face_prev, dR = face - ai;
+            const double dLp = (double)limited_offset(dL, dR), dRp = (double)limited_offset(dR, dL);
+            const double aid = (double)ai;
+            const double Fc = fma(P, dRp, fma(Q, dLp, c * aid));
+            const double Ff = (DIR > 0) ? Fc_prev : (DIR < 0) ? Fc : (pos ? Fc_prev : Fc);
+            if (write) {
+                const __amdgpu_buffer_rsrc_t dst = block_rsrc<ST>(D.pool, slot3 & ~NEWFLAG);
+                double nv;
+                if constexpr (ST == VL_F64) {
+                    nv = a3d + (Ff_prev - Ff);
+                    block_store(dst, lane_off, nv);
+                } else {
+                    // the carry goes into the cell only if the cell holds at least as much
+                    const double base = a3d + (Ff_prev - Ff);
+                    const double cin = (fabs(carry) <= base) ? carry : 0.0;
+                    const double x = base + cin;
+                    if constexpr (ST == VL_F32)
+                        block_store(dst, lane_off, narrow_f32(x, nv));
+                    else
+                        block_store(dst, lane_off, narrow_bf16(x, nv));
+                    carry = (carry - cin) + (x - nv);
+                }
+                if constexpr (LAST) {
+                    const unsigned long long any = __ballot(nv >= smin);
+                    sflag[t - 3] = any ? 1 : 0;
+                }
+            }
+            a3d = aid;
+            a2 = a1;
+            a1 = a;
+            da_prev = da;
+            face_prev = face;
+            Fc_prev = Fc;
+            Ff_prev = Ff;
+        };
+        int i0 = 0;
+        for (; i0 + PFV <= iend; i0 += PFV) {
 #pragma unroll
             for (int u = 0; u < PFV; u++) {
                 cur[u] = (uint32_t)__builtin_amdgcn_readlane((int)win, i0 + u + PFV + WIN0);
                 const C a = q[u];
                 q[u] = fetch_raw(cur[u]);
-                const C dl = a1 - a2, dr = a - a1;
-                const C da = limited_slope2(dl, dr, a - a2);
-                const C face = face_value(a2, a1 - a2, da, da_prev);
-                const C ai = a2;
-                const C dL = ai - face_prev, dR = face - ai;
-                const double dLp = (double)limited_offset(dL, dR), dRp = (double)limited_offset(dR, dL);
-                const double aid = (double)ai;
-                const double Fc = fma(P, dRp, fma(Q, dLp, c * aid));
-                const double Ff = (DIR > 0) ? Fc_prev : (DIR < 0) ? Fc : (pos ? Fc_prev : Fc);
-                if ((wm >> u) & 1ull) {  // cell t - 3
-                    const uint32_t sl3 = (u >= 3) ? prv[u - 3] : bef[u];
-                    const __amdgpu_buffer_rsrc_t dst = block_rsrc<ST>(D.pool, sl3 & ~NEWFLAG);
-                    double nv;
-                    if constexpr (ST == VL_F64) {
-                        nv = a3d + (Ff_prev - Ff);
-                        block_store(dst, lane_off, nv);
-                    } else {
-                        // the carry goes into the cell only if the cell holds at least as much
-                        const double base = a3d + (Ff_prev - Ff);
-                        const double cin = (fabs(carry) <= base) ? carry : 0.0;
-                        const double x = base + cin;
-                        if constexpr (ST == VL_F32)
-                            block_store(dst, lane_off, narrow_f32(x, nv));
-                        else
-                            block_store(dst, lane_off, narrow_bf16(x, nv));
-                        carry = (carry - cin) + (x - nv);
-                    }
-                    if constexpr (LAST) {
-                        const unsigned long long any = __ballot(nv >= smin);
-                        sflag[w0 + i0 + u - 3] = any ? 1 : 0;
-                    }
-                }
-                a3d = aid;
-                a2 = a1;
-                a1 = a;
-                da_prev = da;
-                face_prev = face;
-                Fc_prev = Fc;
-                Ff_prev = Ff;
+                iteration(a, (u >= 3) ? prv[u - 3] : bef[u], (wm >> u) & 1ull, w0 + i0 + u);
             }
             wm >>= PFV;
 #pragma unroll
             for (int i = 0; i < 3; i++) bef[i] = prv[PFV - 3 + i];
 #pragma unroll
             for (int u = 0; u < PFV; u++) prv[u] = cur[u];
+        }
+        // the segment's last iterations, less than a group, with nothing left
+        // to fetch
+        if (i0 < iend) {
+#pragma unroll
+            for (int u = 0; u < PFV - 1; u++)
+                if (i0 + u < iend)
+                    iteration(q[u], (u >= 3) ? prv[u - 3] : bef[u], (wm >> u) & 1ull, w0 + i0 + u);
         }
     }
 }
