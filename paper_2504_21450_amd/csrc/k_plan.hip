@@ -18,6 +18,9 @@
 //      axis's new ledger store and maps each of them to the item of the same
 //      block in the store of the previous shear along the axis (a bitmap
 //      look-up per old item), so the shear can take that line's residual.
+// The mask words of a block are registers of its thread: their number (NW, the
+// line's words rounded up to 1, 2, 4 or 8) is a template parameter, as eight for
+// every line spilled more scalars (8^3 dense cells: 23 -> 19 us a shear).
 // In a periodic partition (template parameter WR) only the local pencils are
 // planned: a pencil's ghost cells are its own first and last cells seen through
 // the period, so their presence bits are copied from those cells' bits, no list
@@ -32,6 +35,7 @@
 // lists it grows.  Block ids of a chunk of the union are processed at a time
 // so the LDS footprint is bounded.
 #include <algorithm>
+#include <type_traits>
 
 #include "vl_internal.h"
 
@@ -52,11 +56,16 @@ struct PlanParams {
 
 __device__ inline int popc(uint32_t v) { return __popc(v); }
 
-// threads and wavefronts of a planner workgroup, and its LDS budget: four
-// workgroups fit a compute unit's 160 KiB (and its registers), and a
-// pencil's union is taken in chunks of as many block ids as the budget holds
-// (larger chunks in fewer, larger workgroups were slower on the mixture)
-constexpr int PNT = 256;
+// Threads and wavefronts of a planner workgroup, and its LDS budget: two
+// workgroups are resident by their registers (120 a thread), and a pencil's
+// union is taken in chunks of as many block ids as the budget holds.  Bound by
+// latency (three quarters of the wave cycles wait) and, on large mixtures, by
+// the scattered row entries it writes.  Eight wavefronts share a pencil's cells
+// rather than four: 256 threads / 512 threads, us a shear: 16x16x8 FP64 98 /
+// 67, 23x17x11 FP32 123 / 85, 24x24x12 BF16 mixture 420 / 306, 64x64x32 FP64
+// 671 / 610; chunks of twice the size gained nothing, and registers cut to 64
+// for four workgroups lost a third.
+constexpr int PNT = 512;
 constexpr int PNW = PNT / 64;
 constexpr size_t PLAN_LDS_BUDGET = 34 * 1024;
 
@@ -122,7 +131,7 @@ __device__ inline void row_or3(uint32_t *row, int pos, uint32_t v)
     if (s > 29) row[w + 1] |= v >> (32 - s);
 }
 
-template <bool WR>
+template <bool WR, int NW>
 __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -273,15 +282,11 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     const int64_t ibp = (int64_t)s_ibp;
 
     // update-range mask
-    uint32_t um[MAXWL];
+    uint32_t um[NW];
 #pragma unroll
-    for (int w = 0; w < MAXWL; w++) {
-        uint32_t m = 0;
-        for (int b = 0; b < 32; b++) {
-            int i = 32 * w + b;
-            if (i >= pp.ulo && i < pp.uhi) m |= 1u << b;
-        }
-        um[w] = m;
+    for (int w = 0; w < NW; w++) {
+        const int lo = min(max(pp.ulo - 32 * w, 0), 32), hi = min(max(pp.uhi - 32 * w, 0), 32);
+        um[w] = hi > lo ? (~0u >> (32 - (hi - lo))) << lo : 0u;
     }
 
     // the cells of a row's word w before bit b
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
         __syncthreads();
         // growth and per-block counts
         for (int k = tid; k < rn; k += PNT) {
-            uint32_t P[MAXWL], G[MAXWL];
+            uint32_t P[NW], G[NW];
             if constexpr (WR) {  // the ghost cells hold what their images hold
                 uint32_t *row = s_pres + k * WL;
                 const uint32_t first = row_bits3(row, H), lst = row_bits3(row, L - 2 * H);
@@ -390,19 +395,19 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 row_or3(row, L - H, first);
             }
 #pragma unroll
-            for (int w = 0; w < MAXWL; w++) P[w] = (w < WL) ? s_pres[k * WL + w] : 0u;
+            for (int w = 0; w < NW; w++) P[w] = (w < WL) ? s_pres[k * WL + w] : 0u;
             const int dirs = block_dirs(D, pp.d, s_id[k], pp.dt);
 #pragma unroll
-            for (int w = 0; w < MAXWL; w++) {
+            for (int w = 0; w < NW; w++) {
                 uint32_t g = 0;
                 if (dirs & 1) g |= (P[w] << 1) | (w > 0 ? (P[w - 1] >> 31) : 0u);
-                if (dirs & 2) g |= (P[w] >> 1) | (w + 1 < MAXWL ? (P[w + 1] << 31) : 0u);
+                if (dirs & 2) g |= (P[w] >> 1) | (w + 1 < NW ? (P[w + 1] << 31) : 0u);
                 G[w] = g & ~P[w] & um[w];
             }
             int rowlen = 0, nnew = 0, upd = 0, rd = 0, own = 0;
             bool active = false;
 #pragma unroll
-            for (int w = 0; w < MAXWL; w++) {
+            for (int w = 0; w < NW; w++) {
                 if (w < WL) {
                     const uint32_t pn = P[w] | G[w];
                     s_pres[k * WL + w] = pn;
@@ -417,7 +422,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             }
             if (nnew > 0) {
 #pragma unroll
-                for (int w = 0; w < MAXWL; w++) {
+                for (int w = 0; w < NW; w++) {
                     uint32_t g = G[w];
                     while (g) {
                         const int bit = __ffs(g) - 1;
@@ -431,7 +436,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
             {
                 int run = 0;
 #pragma unroll
-                for (int w = 0; w < MAXWL; w++) {
+                for (int w = 0; w < NW; w++) {
                     if (w < WL) {
                         s_cum[k * WL + w] = active ? (uint8_t)run : (uint8_t)255;
                         // (WR: no ghosts before the line; those after it precede none of its cells)
@@ -791,14 +796,23 @@ void launch_plan(const Dev &D, int d, int sidx, const int lo[3], const int hi[3]
     if (R < 64) R = 64;
     pp.R = R;
     size_t lds = plan_lds_bytes(D.W, R, pp.WL, pp.L);
-    if (wrap) {
-        const int64_t np = (int64_t)D.n[pp.e1] * D.n[pp.e2];
-        hipLaunchKernelGGL(k_plan<true>, dim3((unsigned)np), dim3(PNT), lds, st, D, pp);
-        return;
-    }
-    int64_t np = (int64_t)pp.n1 * pp.n2;
+    const int64_t np = wrap ? (int64_t)D.n[pp.e1] * D.n[pp.e2] : (int64_t)pp.n1 * pp.n2;
     if (np <= 0) return;
-    hipLaunchKernelGGL(k_plan<false>, dim3((unsigned)np), dim3(PNT), lds, st, D, pp);
+    const dim3 g((unsigned)np);
+    auto launch = [&](auto nw) {
+        if (wrap)
+            hipLaunchKernelGGL((k_plan<true, nw.value>), g, dim3(PNT), lds, st, D, pp);
+        else
+            hipLaunchKernelGGL((k_plan<false, nw.value>), g, dim3(PNT), lds, st, D, pp);
+    };
+    if (pp.WL == 1)
+        launch(std::integral_constant<int, 1>());
+    else if (pp.WL == 2)
+        launch(std::integral_constant<int, 2>());
+    else if (pp.WL <= 4)
+        launch(std::integral_constant<int, 4>());
+    else
+        launch(std::integral_constant<int, MAXWL>());
 }
 
 }  // namespace vl
