@@ -575,6 +575,8 @@ int vl_init_partition(const vl_desc *d, void *dev_workspace, size_t ws_bytes, vo
             if (hipMemcpy(D.lid, lid.data(), lid.size() * 4, hipMemcpyHostToDevice) != hipSuccess) { rc = VL_ERR_HIP; break; }
             if (hipMemcpy(D.lslot, lslot.data(), lslot.size() * 4, hipMemcpyHostToDevice) != hipSuccess) { rc = VL_ERR_HIP; break; }
         }
+        // the moments' unit counters (each pass leaves them at zero)
+        if (hipMemset(p->mom.ctr, 0, 16) != hipSuccess) { rc = VL_ERR_HIP; break; }
         // empty ledger stores: no line has a residual yet
         if (L.lg_cap > 0) {
             bool ok = true;

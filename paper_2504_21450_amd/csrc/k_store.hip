@@ -345,19 +345,17 @@ void launch_cell_counts(const Dev &D, hipStream_t st)
 // mixture are spread over many wavefronts.  A unit of a cell with one chunk
 // writes the cell's moments; the units of a split cell leave ten partial sums
 // each, which the cell's combine pass adds in chunk order (the same result in
-// every run).  Per block the lanes add f, f k, f k k^T with k the block
-// centre's offset from R in units of 4 dv per axis (uniform over the block,
-// computed from the two blocks' packed coordinates; the units are applied to
-// the sums at the end);
+// every run).  With k the block centre's offset from R in units of 4 dv per
+// axis (uniform over the block, from the two blocks' packed coordinates; the
+// units are applied to the sums at the end), the lanes add f, f kx and f kx^2
+// per block, and when the sorted list goes on to another row of blocks (ky or
+// kz changes) the row's three sums enter the ten sums of f, f k, f k k^T: the
+// kernel is bound by FP64 vector instructions, and these are 9 a block and 10
+// a row (4 to 25 blocks) instead of 18 a block: 1.84 -> 1.41 ms for the 28
+// million BF16 blocks of a 48x48x24 mixture (0.75 ms at the rate of a copy).
 // each lane's offset o within the block enters once at the end:
 //   sum f (c + o) = S1c + o S0,  sum f (c+o)(c+o)^T = S2c + S1c o^T + o S1c^T + S0 o o^T.
 // ---------------------------------------------------------------------------
-__device__ inline double wave_sum_d(double v)
-{
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-
 // packed block coordinates bx | by << 10 | bz << 20
 __device__ inline int32_t pack_coords(const Dev &D, int32_t id)
 {
@@ -397,16 +395,6 @@ __device__ inline void reference_velocity(const Dev &D, int32_t idR, int cnt, do
     for (int a = 0; a < 3; a++) R[a] = cnt > 0 ? D.vmin[a] + (4 * b[a] + 2) * D.dv[a] : 0.0;
 }
 
-// counters to zero (a kernel, not a memset, so graph captures replay it
-// faithfully)
-__global__ __launch_bounds__(256) void k_mom_reset(MomScratch M)
-{
-    if (threadIdx.x == 0) {
-        M.ctr[0] = 0ull;
-        M.ctr[1] = 0ull;
-    }
-}
-
 // per local cell: the partial slots of a split cell and its further chunks
 __global__ __launch_bounds__(256) void k_mom_plan(Dev D, MomScratch M)
 {
@@ -436,14 +424,14 @@ __global__ __launch_bounds__(256) void k_mom_plan(Dev D, MomScratch M)
 // where five would spill
 template <int ST>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F64 ? 4 : 5))) void k_mom_units(
-    Dev D, MomScratch M, double *dn, double *dV, double *dP)
+    Dev D, MomScratch M, bool split, double *dn, double *dV, double *dP)
 {
     if (failed(D)) return;
     const int lane = threadIdx.x & 63;
     // the wavefront's index, made visibly uniform so the unit's cell and its
     // metadata are read with scalar loads
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nunits = D.nlocal + (int64_t)min(M.ctr[1], (unsigned long long)M.cap_extra);
+    const int64_t nunits = D.nlocal + (split ? (int64_t)min(M.ctr[1], (unsigned long long)M.cap_extra) : 0);
     const int64_t nwaves = (int64_t)gridDim.x * 4;
     // raw storage words, widened when summed (BF16 bits held in 32-bit
     // registers, which the compiler does not pack in pairs)
@@ -480,28 +468,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
         // axis (k, uniform over the block, from the packed coordinates in
         // scalar registers); the units are applied once per unit below
         double s0 = 0.0, s1[3] = {0.0, 0.0, 0.0}, s2[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        // the current row's sums of f, f kx, f kx^2
+        double r0 = 0.0, r1 = 0.0, r2 = 0.0;
+        int32_t rowpk = pkR;  // packed coordinates of a block of the row
+        auto end_row = [&]() {
+            const double ky = (double)(((rowpk >> 10) & 1023) - ((pkR >> 10) & 1023));
+            const double kz = (double)((rowpk >> 20) - (pkR >> 20));
+            s0 += r0;
+            s1[0] += r1;
+            s1[1] = fma(ky, r0, s1[1]);
+            s1[2] = fma(kz, r0, s1[2]);
+            s2[0] += r2;
+            s2[1] = fma(ky * ky, r0, s2[1]);
+            s2[2] = fma(kz * kz, r0, s2[2]);
+            s2[3] = fma(ky, r1, s2[3]);
+            s2[4] = fma(kz, r1, s2[4]);
+            s2[5] = fma(ky * kz, r0, s2[5]);
+            r0 = r1 = r2 = 0.0;
+        };
         auto acc = [&](double f, int32_t pk) {
+            if ((pk ^ rowpk) >> 10) end_row();
+            rowpk = pk;
             const double kx = (double)((pk & 1023) - (pkR & 1023));
-            const double ky = (double)(((pk >> 10) & 1023) - ((pkR >> 10) & 1023));
-            const double kz = (double)((pk >> 20) - (pkR >> 20));
-            const double fx = f * kx, fy = f * ky, fz = f * kz;
-            s0 += f;
-            s1[0] += fx;
-            s1[1] += fy;
-            s1[2] += fz;
-            s2[0] = fma(fx, kx, s2[0]);
-            s2[1] = fma(fy, ky, s2[1]);
-            s2[2] = fma(fz, kz, s2[2]);
-            s2[3] = fma(fx, ky, s2[3]);
-            s2[4] = fma(fx, kz, s2[4]);
-            s2[5] = fma(fy, kz, s2[5]);
+            const double fx = f * kx;
+            r0 += f;
+            r1 += fx;
+            r2 = fma(fx, kx, r2);
         };
         for (int g = b0; g < b1; g += 64) {
             // slots and packed coordinates of up to 64 blocks, one per lane;
             // past the list the all-zero block (f = 0 adds nothing)
             const int ng = min(64, b1 - g);
             const uint32_t myslot = lane < ng ? (uint32_t)D.lslot[ls + g + lane] : zslot;
-            const int32_t mypk = lane < ng ? pack_coords(D, D.lid[ls + g + lane]) : pkR;
+            // (past the list: the last block's, so that no row ends there)
+            const int32_t mypk = pack_coords(D, D.lid[ls + g + min(lane, ng - 1)]);
             // groups of NF blocks, the next group's loads issued before the
             // current group is summed (every load is issued: blocks past the
             // 64 read the all-zero block)
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
                 for (int i = 0; i < NF; i++) {
                     const int k = k0 + i;
                     const int32_t rl = __builtin_amdgcn_readlane(mypk, k & 63);
-                    acc(Storage<ST>::widen((T)r[i]), k < 64 ? rl : pkR);
+                    acc(Storage<ST>::widen((T)r[i]), k < 64 ? rl : rowpk);
                 }
             };
             // (scheduling barriers keep each group's loads where they are
@@ -538,6 +538,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        end_row();
         // the block offsets' units (4 dv per axis)
         const double ux = 4.0 * D.dv[0], uy = 4.0 * D.dv[1], uz = 4.0 * D.dv[2];
         s1[0] *= ux;
@@ -559,8 +560,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
         S[7] = s2[3] + o[0] * s1[1] + o[1] * s1[0] + o[0] * o[1] * s0;
         S[8] = s2[4] + o[0] * s1[2] + o[2] * s1[0] + o[0] * o[2] * s0;
         S[9] = s2[5] + o[1] * s1[2] + o[2] * s1[1] + o[1] * o[2] * s0;
-        for (int i = 0; i < 10; i++) S[i] = wave_sum_d(S[i]);
-        const int32_t base = M.cell_base[q];
+        for (int i = 0; i < 10; i++) S[i] = wave_sum_f64(S[i]);
+        const int32_t base = split ? M.cell_base[q] : -1;
         if (base < 0) {
             if (lane == 0) moments_finish(D, q, S, R, dn, dV, dP, M.cell_mass);
         } else if (lane < 10) {
@@ -571,10 +572,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
     }
 }
 
-// per split cell: its chunks' partial sums added in chunk order
+// per split cell: its chunks' partial sums added in chunk order; the unit
+// counters go back to zero for the next pass (a kernel, not a memset, so graph
+// captures replay it faithfully)
 __global__ __launch_bounds__(256) void k_mom_combine(Dev D, MomScratch M, double *dn, double *dV, double *dP)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q < 2) M.ctr[q] = 0ull;
     if (q >= D.nlocal || failed(D)) return;
     const int32_t base = M.cell_base[q];
     if (base < 0) return;
@@ -609,24 +613,27 @@ static unsigned resident_groups(K kernel)
 }
 
 template <int ST>
-static void launch_mom_units(const Dev &D, const MomScratch &M, double *dn, double *dV, double *dP, hipStream_t st)
+static void launch_mom_units(const Dev &D, const MomScratch &M, bool split, double *dn, double *dV, double *dP,
+                             hipStream_t st)
 {
     static const unsigned g = resident_groups(k_mom_units<ST>);
-    hipLaunchKernelGGL(k_mom_units<ST>, dim3(g), dim3(256), 0, st, D, M, dn, dV, dP);
+    hipLaunchKernelGGL(k_mom_units<ST>, dim3(g), dim3(256), 0, st, D, M, split, dn, dV, dP);
 }
 
 void launch_moments(const Dev &D, const MomScratch &M, double *dn, double *dV, double *dP, hipStream_t st)
 {
     if (D.nlocal <= 0) return;
     const dim3 gc((unsigned)((D.nlocal + 255) / 256));
-    hipLaunchKernelGGL(k_mom_reset, dim3(1), dim3(256), 0, st, M);
-    hipLaunchKernelGGL(k_mom_plan, gc, dim3(256), 0, st, D, M);
+    // no cell of a mesh of at most one chunk of blocks is split: one launch
+    // (of 8^3 dense cells' 25 us of moments, 13 were the other three)
+    const bool split = D.NB > M.chunk;
+    if (split) hipLaunchKernelGGL(k_mom_plan, gc, dim3(256), 0, st, D, M);
     switch (D.storage) {
-    case VL_F64: launch_mom_units<VL_F64>(D, M, dn, dV, dP, st); break;
-    case VL_F32: launch_mom_units<VL_F32>(D, M, dn, dV, dP, st); break;
-    default: launch_mom_units<VL_BF16>(D, M, dn, dV, dP, st); break;
+    case VL_F64: launch_mom_units<VL_F64>(D, M, split, dn, dV, dP, st); break;
+    case VL_F32: launch_mom_units<VL_F32>(D, M, split, dn, dV, dP, st); break;
+    default: launch_mom_units<VL_BF16>(D, M, split, dn, dV, dP, st); break;
     }
-    hipLaunchKernelGGL(k_mom_combine, gc, dim3(256), 0, st, D, M, dn, dV, dP);
+    if (split) hipLaunchKernelGGL(k_mom_combine, gc, dim3(256), 0, st, D, M, dn, dV, dP);
 }
 
 // ---------------------------------------------------------------------------
