@@ -1166,49 +1166,72 @@ int vl_export_state(vl_partition *p, int64_t *cell_offsets, int32_t *block_ids, 
     const Dev &D = p->D;
     int rc = device_status(p);
     if (rc) return rc;
-    // bulk metadata copy, then per-cell assembly on the host
-    std::vector<int64_t> lstart((size_t)D.N);
-    std::vector<int32_t> lcount((size_t)D.N);
-    VL_HIP(hipMemcpy(lstart.data(), D.lstart, (size_t)D.N * 8, hipMemcpyDeviceToHost));
+    // bulk metadata copy; the lists are packed on the device
+    std::vector<int32_t> lcount((size_t)D.N), lsorted((size_t)D.N);
     VL_HIP(hipMemcpy(lcount.data(), D.lcount, (size_t)D.N * 4, hipMemcpyDeviceToHost));
-    const int64_t roff = D.reg_off[p->cur], rcap = D.reg_cap[p->cur];
-    std::vector<int32_t> lid((size_t)rcap), lslot((size_t)rcap);
-    VL_HIP(hipMemcpy(lid.data(), D.lid + roff, (size_t)rcap * 4, hipMemcpyDeviceToHost));
-    VL_HIP(hipMemcpy(lslot.data(), D.lslot + roff, (size_t)rcap * 4, hipMemcpyDeviceToHost));
+    VL_HIP(hipMemcpy(lsorted.data(), D.lsorted, (size_t)D.N * 4, hipMemcpyDeviceToHost));
     int64_t total = 0;
+    bool sorted = true;
     cell_offsets[0] = 0;
     for (int64_t q = 0; q < D.nlocal; q++) {
         const int x = (int)(q % D.n[0]), y = (int)((q / D.n[0]) % D.n[1]), z = (int)(q / ((int64_t)D.n[0] * D.n[1]));
-        total += lcount[cell_index(D, x + H, y + H, z + H)];
+        const int64_t c = cell_index(D, x + H, y + H, z + H);
+        total += lcount[c];
+        sorted = sorted && lsorted[c] == lcount[c];
         cell_offsets[q + 1] = total;
     }
     if (total > cap_blocks) return VL_ERR_ARG;
     if (total > 0 && !block_ids) return VL_ERR_ARG;
-    std::vector<int32_t> slots((size_t)total);
-    std::vector<std::pair<int32_t, int32_t>> ent;
-    for (int64_t q = 0; q < D.nlocal; q++) {
-        const int x = (int)(q % D.n[0]), y = (int)((q / D.n[0]) % D.n[1]), z = (int)(q / ((int64_t)D.n[0] * D.n[1]));
-        const int64_t c = cell_index(D, x + H, y + H, z + H);
-        const int64_t s0 = lstart[c] - roff;
-        const int cnt = lcount[c];
-        if (cnt > 0 && (s0 < 0 || s0 + cnt > rcap)) return VL_ERR_STATE;
-        ent.resize(cnt);
-        for (int k = 0; k < cnt; k++) ent[k] = {lid[s0 + k], lslot[s0 + k]};
-        std::sort(ent.begin(), ent.end());
-        for (int k = 0; k < cnt; k++) {
-            block_ids[cell_offsets[q] + k] = ent[k].first;
-            slots[cell_offsets[q] + k] = ent[k].second;
-        }
-    }
-    const int64_t chunk = std::min<int64_t>((int64_t)(p->lay.row_cap * 4) / (BLK * 8),
-                                            (int64_t)(p->lay.item_cap * sizeof(Item)) / 4);
-    if (chunk < 1) return VL_ERR_STATE;
+    if (total == 0) return VL_OK;
+    // Dead buffers hold the lists' offsets (per-cell sums), the packed slots
+    // (work items) and the packed ids, then the FP64 values (rows).  A partition
+    // has fewer blocks than row entries; the item array of a very large one may
+    // not hold every slot, and lists that are not in order (none after a step)
+    // are ordered on the host: then the slots make the round trip in pieces, as
+    // the values do.  (A step with the state of 7x5x3 sparse cells taken to the
+    // host: 7.4 ms with the whole list region copied and every cell's list
+    // sorted on the host, 6.5 ms so; the rest is the 53 MB of values.)
+    const int64_t item_i32 = (int64_t)(p->lay.item_cap * sizeof(Item)) / 4;
+    if (total > p->lay.row_cap) return VL_ERR_STATE;  // (not reached)
+    int64_t *doff = (int64_t *)D.cell_red;
     int32_t *dslots = (int32_t *)D.items;
     double *dvals = (double *)D.rows;
+    const bool resident = sorted && total <= item_i32;
+    VL_HIP(hipMemcpyAsync(doff, cell_offsets, (size_t)D.nlocal * 8, hipMemcpyHostToDevice, p->stream));
+    std::vector<int32_t> slots;
+    if (resident) {
+        launch_pack_lists(D, doff, D.rows, dslots, p->stream);
+        VL_HIP(hipGetLastError());
+        VL_HIP(hipMemcpyAsync(block_ids, D.rows, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
+        VL_HIP(hipStreamSynchronize(p->stream));
+    } else {
+        // (the list entry -> item array is dead here as well)
+        launch_pack_lists(D, doff, D.rows, D.litem, p->stream);
+        VL_HIP(hipGetLastError());
+        slots.resize((size_t)total);
+        VL_HIP(hipMemcpyAsync(block_ids, D.rows, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
+        VL_HIP(hipMemcpyAsync(slots.data(), D.litem, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
+        VL_HIP(hipStreamSynchronize(p->stream));
+        std::vector<std::pair<int32_t, int32_t>> ent;
+        for (int64_t q = 0; q < D.nlocal; q++) {
+            const int64_t b0 = cell_offsets[q], b1 = cell_offsets[q + 1];
+            ent.resize((size_t)(b1 - b0));
+            for (int64_t k = b0; k < b1; k++) ent[(size_t)(k - b0)] = {block_ids[k], slots[(size_t)k]};
+            std::sort(ent.begin(), ent.end());
+            for (int64_t k = b0; k < b1; k++) {
+                block_ids[k] = ent[(size_t)(k - b0)].first;
+                slots[(size_t)k] = ent[(size_t)(k - b0)].second;
+            }
+        }
+    }
+    const int64_t chunk = std::min<int64_t>((int64_t)(p->lay.row_cap * 4) / (BLK * 8), item_i32);
+    if (chunk < 1) return VL_ERR_STATE;
     for (int64_t o = 0; o < total; o += chunk) {
         const int64_t m = std::min(chunk, total - o);
-        VL_HIP(hipMemcpyAsync(dslots, slots.data() + o, (size_t)m * 4, hipMemcpyHostToDevice, p->stream));
-        launch_gather(D, dslots, m, dvals, p->stream);
+        const int32_t *at = dslots + (resident ? o : 0);
+        if (!resident)
+            VL_HIP(hipMemcpyAsync(dslots, slots.data() + o, (size_t)m * 4, hipMemcpyHostToDevice, p->stream));
+        launch_gather(D, at, m, dvals, p->stream);
         VL_HIP(hipGetLastError());
         VL_HIP(hipMemcpyAsync(f + o * BLK, dvals, (size_t)m * BLK * 8, hipMemcpyDeviceToHost, p->stream));
         VL_HIP(hipStreamSynchronize(p->stream));

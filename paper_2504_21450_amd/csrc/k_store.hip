@@ -683,6 +683,27 @@ MomScratch carve_moments_scratch(void *base, int64_t nlocal, int64_t parts, int6
     return M;
 }
 
+// lists of the local cells packed for the host, one wavefront per cell
+__global__ __launch_bounds__(256) void k_pack_lists(Dev D, const int64_t *offsets, int32_t *ids, int32_t *slots)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (q >= D.nlocal) return;
+    int x, y, z;
+    local_coords(D, q, x, y, z);
+    const int64_t c = cell_index(D, x + H, y + H, z + H), ls = D.lstart[c], to = offsets[q];
+    const int cnt = D.lcount[c];
+    for (int e = lane; e < cnt; e += 64) {
+        ids[to + e] = D.lid[ls + e];
+        slots[to + e] = D.lslot[ls + e];
+    }
+}
+
+void launch_pack_lists(const Dev &D, const int64_t *offsets, int32_t *ids, int32_t *slots, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_pack_lists, dim3((unsigned)((D.nlocal + 3) / 4)), dim3(256), 0, st, D, offsets, ids, slots);
+}
+
 // gather blocks (by slot) into a dense FP64 array, one wavefront per block
 template <int ST>
 __global__ __launch_bounds__(256) void k_gather(Dev D, const int32_t *slots, int64_t n, double *out)

@@ -284,6 +284,9 @@ int static_moments_scratch(void **ptr);
 constexpr int64_t STATIC_MOMENTS_SCRATCH_BYTES = 64ll << 20;
 void launch_cell_counts(const Dev &D, hipStream_t st);
 void launch_gather(const Dev &D, const int32_t *slots, int64_t n, double *out, hipStream_t st);
+// the lists of local cells (all of them, in order), one after another: ids and
+// slots of cell q at offsets[q]
+void launch_pack_lists(const Dev &D, const int64_t *offsets, int32_t *ids, int32_t *slots, hipStream_t st);
 
 // book-keeping operations (launch_book)
 enum {
