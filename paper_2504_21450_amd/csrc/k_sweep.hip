@@ -72,9 +72,8 @@ __device__ __forceinline__ uint32_t wrap_slot(const Dev &D, int place)
 // for the march has read them before it writes its first cell; those after
 // the line are its first cells, which the march has overwritten by then, so
 // their old values are copied aside first (three blocks, which stay in the
-// cache; place: 0 or WRAP).  A block created in this shear is not held by the
-// images yet.  The copies' latency, once per item, costs less than a test in
-// each of the line's iterations would.
+// cache; place: 0 or WRAP), so that the marches need no test for the line's
+// end.  A block created in this shear is not held by the images yet.
 template <int ST>
 __device__ __forceinline__ void wrap_slots(const Dev &D, uint32_t *srow, int L, int n, int lane, int place)
 {
