@@ -81,3 +81,32 @@ def test_moments_of_empty_and_single_block_cells():
     assert np.max(np.abs(dn - on)) <= 1e-12 * np.max(on)
     assert np.max(np.abs(dV - oV)) <= 1e-12 * np.max(np.abs(oV))
     assert np.max(np.abs(dP - oP)) <= 1e-11 * np.max(np.abs(oP[:, :3]))
+
+
+@pytest.mark.parametrize("storage", [B.VL_F64, B.VL_F32, B.VL_BF16])
+@pytest.mark.parametrize("nblk", [(20, 9, 11), (1, 40, 50)])
+def test_moments_of_scattered_and_compact_blocks(nblk, storage):
+    """The sums go by rows of blocks where 64 listed blocks hold runs of
+    consecutive ids and block by block where they are scattered: cells of
+    scattered blocks, of runs, and of both in turn, with lists that end within
+    and at a multiple of 64 blocks and in the second chunk of 1024, on a
+    velocity mesh with long rows and on one whose rows are single blocks.
+    Tolerances as in the file's other tests."""
+    need_gpu()
+    n, NB = (3, 3, 1), int(np.prod(nblk))
+    rng = np.random.default_rng(57)
+    spread = np.sort(rng.choice(NB, 64 * 6 + 5, replace=False))
+    lists = [np.arange(100, 164), np.arange(0, NB, 2)[:128], spread, np.arange(NB), np.array([NB - 1]),
+             np.union1d(np.arange(300, 300 + 70), np.arange(500, NB, 7)[:70]),
+             np.union1d(np.arange(0, 500, 3), np.arange(500, 500 + 190)),
+             np.sort(rng.choice(NB, 1024 + 65, replace=False)),
+             np.delete(np.arange(NB), np.arange(5, NB, 2)[:31])]
+    off = np.zeros(len(lists) + 1, np.int64)
+    off[1:] = np.cumsum([a.size for a in lists])
+    ids = np.concatenate(lists).astype(np.int32)
+    state = (off, ids, rng.uniform(1e-10, 1e-9, ids.size * 64))
+    w = W.Workload("rows", n, (200.0,) * 3, nblk, tuple(-2.0 * b for b in nblk), (1.0, 1.0, 1.0), 1.0, 1, 0.0, 0,
+                   B.VL_F64, (0, 1, 2), *state)
+    print_case("moments of scattered and compact blocks, mesh %s, storage %d" % (nblk, storage))
+    p = gpu_partition(w, storage=storage)
+    check(p, w, p.export())
