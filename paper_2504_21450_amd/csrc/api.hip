@@ -624,6 +624,9 @@ int vl_init_partition(const vl_desc *d, void *dev_workspace, size_t ws_bytes, vo
             }
             if (rc) break;
         }
+        // the clears above were given to the null stream, which a stream made
+        // without its blocking does not wait for, and may still be under way
+        if (hipStreamSynchronize(nullptr) != hipSuccess) { rc = VL_ERR_HIP; break; }
         launch_iota_ring(D, total, D.lcap - total, p->stream);
         if (hipGetLastError() != hipSuccess) { rc = VL_ERR_HIP; break; }
         if (hipStreamSynchronize(p->stream) != hipSuccess) { rc = VL_ERR_HIP; break; }
