@@ -353,12 +353,13 @@ void launch_cell_counts(const Dev &D, hipStream_t st)
 // kernel is bound by FP64 vector instructions, and these are 9 a block and 10
 // a row (4 to 25 blocks) instead of 18 a block: 1.84 -> 1.41 ms for the 28
 // million BF16 blocks of a 48x48x24 mixture (0.75 ms at the rate of a copy).
-// Where blocks are scattered, or the mesh is one block thick along x, every
-// block ends a row, which costs more than the 18: 64 listed blocks whose runs
-// of consecutive ids are shorter than two on average are summed one by one
-// (300 blocks in each of 32x32x16 cells, by rows / so: scattered BF16 347 / 331
-// us, FP64 504 / 496, a mesh of 1x64x64 blocks 373 / 323; the test of the ids
-// costs the mixture 0.4 %).
+// On a mesh of one or two blocks along x nearly every block ends a row, which
+// costs more than the 18, so there each block enters the ten sums by itself
+// (template parameter ROWS; 300 blocks in each of 32x32x16 cells on a mesh of
+// 1x64x64 blocks, BF16: 360 -> 312 us).  Lists of isolated blocks on other
+// meshes, which neither sampling nor pruning leaves, are summed by rows as
+// well: choosing by the ids of the list made them 6 % faster and every other
+// list 2 to 8 % slower (registers and one more test per 64 blocks).
 // each lane's offset o within the block enters once at the end:
 //   sum f (c + o) = S1c + o S0,  sum f (c+o)(c+o)^T = S2c + S1c o^T + o S1c^T + S0 o o^T.
 // ---------------------------------------------------------------------------
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(256) void k_mom_plan(Dev D, MomScratch M)
 // five waves per SIMD for the narrow storage types (95 VGPRs, 37.6 instead of
 // 39.5 ms per step on the 128x128x64 BF16 mixture); FP64 keeps the default,
 // where five would spill
-template <int ST>
+template <int ST, bool ROWS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F64 ? 4 : 5))) void k_mom_units(
     Dev D, MomScratch M, bool split, double *dn, double *dV, double *dP)
 {
@@ -446,6 +447,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
     constexpr int NF = 8;  // blocks per group; two groups are in flight
     const uint32_t lane_off = (uint32_t)lane * Storage<ST>::BYTES;
     const uint32_t zslot = (uint32_t)D.trash;  // the all-zero block
+    // the lane's velocity offset from its block's centre
+    const double o[3] = {((lane & 3) - 1.5) * D.dv[0], (((lane >> 2) & 3) - 1.5) * D.dv[1],
+                         ((lane >> 4) - 1.5) * D.dv[2]};
     for (int64_t u = (int64_t)blockIdx.x * 4 + wv; u < nunits; u += nwaves) {
         int64_t q;
         int j;
@@ -490,30 +494,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
             r0 = r1 = r2 = 0.0;
         };
         auto acc = [&](double f, int32_t pk) {
-            if ((pk ^ rowpk) >> 10) end_row();
-            rowpk = pk;
             const double kx = (double)((pk & 1023) - (pkR & 1023));
-            const double fx = f * kx;
-            r0 += f;
-            r1 += fx;
-            r2 = fma(fx, kx, r2);
-        };
-        // a block by itself
-        auto acc1 = [&](double f, int32_t pk) {
-            const double kx = (double)((pk & 1023) - (pkR & 1023));
-            const double ky = (double)(((pk >> 10) & 1023) - ((pkR >> 10) & 1023));
-            const double kz = (double)((pk >> 20) - (pkR >> 20));
-            const double fx = f * kx, fy = f * ky, fz = f * kz;
-            s0 += f;
-            s1[0] += fx;
-            s1[1] += fy;
-            s1[2] += fz;
-            s2[0] = fma(fx, kx, s2[0]);
-            s2[1] = fma(fy, ky, s2[1]);
-            s2[2] = fma(fz, kz, s2[2]);
-            s2[3] = fma(fx, ky, s2[3]);
-            s2[4] = fma(fx, kz, s2[4]);
-            s2[5] = fma(fy, kz, s2[5]);
+            if constexpr (ROWS) {
+                if ((pk ^ rowpk) >> 10) end_row();
+                rowpk = pk;
+                const double fx = f * kx;
+                r0 += f;
+                r1 += fx;
+                r2 = fma(fx, kx, r2);
+            } else {
+                const double ky = (double)(((pk >> 10) & 1023) - ((pkR >> 10) & 1023));
+                const double kz = (double)((pk >> 20) - (pkR >> 20));
+                const double fx = f * kx, fy = f * ky, fz = f * kz;
+                s0 += f;
+                s1[0] += fx;
+                s1[1] += fy;
+                s1[2] += fz;
+                s2[0] = fma(fx, kx, s2[0]);
+                s2[1] = fma(fy, ky, s2[1]);
+                s2[2] = fma(fz, kz, s2[2]);
+                s2[3] = fma(fx, ky, s2[3]);
+                s2[4] = fma(fx, kz, s2[4]);
+                s2[5] = fma(fy, kz, s2[5]);
+            }
         };
         for (int g = b0; g < b1; g += 64) {
             // slots and packed coordinates of up to 64 blocks, one per lane;
@@ -521,7 +524,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
             const int ng = min(64, b1 - g);
             const uint32_t myslot = lane < ng ? (uint32_t)D.lslot[ls + g + lane] : zslot;
             // (past the list: the last block's, so that no row ends there)
-            const int32_t myid = D.lid[ls + g + min(lane, ng - 1)];
+            const int32_t mypk = pack_coords(D, D.lid[ls + g + min(lane, ng - 1)]);
             // groups of NF blocks, the next group's loads issued before the
             // current group is summed (every load is issued: blocks past the
             // 64 read the all-zero block)
@@ -536,43 +539,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
                     r[i] = block_load_raw<ST>(block_rsrc<ST>(D.pool, sl), lane_off);
                 }
             };
-            auto sum_all = [&](auto add) {
-                issue(ra, 0);
-                const int32_t mypk = pack_coords(D, myid);
-                auto take = [&](const RW (&r)[NF], int k0) {
+            auto take = [&](const RW (&r)[NF], int k0) {
 #pragma unroll
-                    for (int i = 0; i < NF; i++) {
-                        const int k = k0 + i;
-                        const int32_t rl = __builtin_amdgcn_readlane(mypk, k & 63);
-                        add(Storage<ST>::widen((T)r[i]), k < 64 ? rl : rowpk);
-                    }
-                };
-                // (scheduling barriers keep each group's loads where they are
-                // issued, ahead of the other group's sums)
-                for (int k0 = 0; k0 < ng; k0 += 2 * NF) {
-                    issue(rb, k0 + NF);
-                    __builtin_amdgcn_sched_barrier(0);
-                    take(ra, k0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    issue(ra, k0 + 2 * NF);
-                    __builtin_amdgcn_sched_barrier(0);
-                    take(rb, k0 + NF);
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int i = 0; i < NF; i++) {
+                    const int k = k0 + i;
+                    const int32_t rl = __builtin_amdgcn_readlane(mypk, k & 63);
+                    acc(Storage<ST>::widen((T)r[i]), k < 64 ? rl : rowpk);
                 }
-                rowpk = __builtin_amdgcn_readlane(mypk, ng - 1);
             };
-            // runs of consecutive ids that begin among the 64 blocks (but the
-            // first block of each 16 lanes is not looked at), about its rows
-            const int32_t previd = __builtin_amdgcn_update_dpp(myid - 1, myid, 0x111, 0xf, 0xf, false);  // row_shr:1
-            const int begun = __popcll(__ballot(lane < ng && myid - previd != 1));
-            if (2 * begun < ng) {
-                sum_all(acc);
-            } else {
-                end_row();
-                sum_all(acc1);
+            // (scheduling barriers keep each group's loads where they are
+            // issued, ahead of the other group's sums)
+            issue(ra, 0);
+            for (int k0 = 0; k0 < ng; k0 += 2 * NF) {
+                issue(rb, k0 + NF);
+                __builtin_amdgcn_sched_barrier(0);
+                take(ra, k0);
+                __builtin_amdgcn_sched_barrier(0);
+                issue(ra, k0 + 2 * NF);
+                __builtin_amdgcn_sched_barrier(0);
+                take(rb, k0 + NF);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        end_row();
+        if constexpr (ROWS) end_row();
         // the block offsets' units (4 dv per axis)
         const double ux = 4.0 * D.dv[0], uy = 4.0 * D.dv[1], uz = 4.0 * D.dv[2];
         s1[0] *= ux;
@@ -584,13 +573,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ST == VL_F6
         s2[3] *= ux * uy;
         s2[4] *= ux * uz;
         s2[5] *= uy * uz;
-        // the lane's velocity offset from its block's centre (its index passed
-        // through an empty asm, so that the offsets are formed here and not held
-        // in registers through the sums), then the sums over the lanes
-        int ln = lane;
-        __asm__ volatile("" : "+v"(ln));
-        const double o[3] = {((ln & 3) - 1.5) * D.dv[0], (((ln >> 2) & 3) - 1.5) * D.dv[1],
-                             ((ln >> 4) - 1.5) * D.dv[2]};
+        // the lane's offset within its block, then the sums over the lanes
         double S[10];
         S[0] = s0;
         for (int a = 0; a < 3; a++) S[1 + a] = s1[a] + o[a] * s0;
@@ -652,12 +635,12 @@ static unsigned resident_groups(K kernel)
     return (unsigned)(per * ncu);
 }
 
-template <int ST>
+template <int ST, bool ROWS>
 static void launch_mom_units(const Dev &D, const MomScratch &M, bool split, double *dn, double *dV, double *dP,
                              hipStream_t st)
 {
-    static const unsigned g = resident_groups(k_mom_units<ST>);
-    hipLaunchKernelGGL(k_mom_units<ST>, dim3(g), dim3(256), 0, st, D, M, split, dn, dV, dP);
+    static const unsigned g = resident_groups(k_mom_units<ST, ROWS>);
+    hipLaunchKernelGGL((k_mom_units<ST, ROWS>), dim3(g), dim3(256), 0, st, D, M, split, dn, dV, dP);
 }
 
 void launch_moments(const Dev &D, const MomScratch &M, double *dn, double *dV, double *dP, hipStream_t st)
@@ -668,11 +651,17 @@ void launch_moments(const Dev &D, const MomScratch &M, double *dn, double *dV, d
     // (of 8^3 dense cells' 25 us of moments, 13 were the other three)
     const bool split = D.NB > M.chunk;
     if (split) hipLaunchKernelGGL(k_mom_plan, gc, dim3(256), 0, st, D, M);
-    switch (D.storage) {
-    case VL_F64: launch_mom_units<VL_F64>(D, M, split, dn, dV, dP, st); break;
-    case VL_F32: launch_mom_units<VL_F32>(D, M, split, dn, dV, dP, st); break;
-    default: launch_mom_units<VL_BF16>(D, M, split, dn, dV, dP, st); break;
-    }
+    auto units = [&](auto rows) {
+        switch (D.storage) {
+        case VL_F64: launch_mom_units<VL_F64, rows.value>(D, M, split, dn, dV, dP, st); break;
+        case VL_F32: launch_mom_units<VL_F32, rows.value>(D, M, split, dn, dV, dP, st); break;
+        default: launch_mom_units<VL_BF16, rows.value>(D, M, split, dn, dV, dP, st); break;
+        }
+    };
+    if (D.nblk[0] > 2)
+        units(std::true_type());
+    else
+        units(std::false_type());
     if (split) hipLaunchKernelGGL(k_mom_combine, gc, dim3(256), 0, st, D, M, dn, dV, dP);
 }
 
