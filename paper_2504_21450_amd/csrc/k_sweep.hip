@@ -163,26 +163,15 @@ __device__ __forceinline__ C clamp_min0(C x, C y)
         return fmax((C)0, fmin(x, y));
 }
 
-// limited slope of a cell (CW84 eq. 1.7-1.8) from its one-sided differences
-// dl, dr and central difference cen: cen limited to twice either one-sided
-// difference, zero at an extremum.  In FP32 it is minmod(cen, minmod(2 dl,
-// 2 dr)) with minmod(x, y) = median(x, y, 0) (the smaller magnitude when x
-// and y share a sign, else zero): two median-of-three instructions, the same
-// value as the general form (which FP64 keeps) up to the sign of a zero.
-template <typename C>
-__device__ __forceinline__ C limited_slope(C dl, C dr, C cen)
-{
-    if constexpr (std::is_same<C, float>::value) {
-        return __builtin_amdgcn_fmed3f(cen, __builtin_amdgcn_fmed3f(2.0f * dl, 2.0f * dr, 0.0f), 0.0f);
-    } else {
-        const C s2 = copysign((C)2.0, cen);
-        const C m = fmax((C)0, fmin(fmin(fabs(cen), s2 * dl), s2 * dr));
-        return copysign(m, cen);
-    }
-}
-
-// twice the limited slope, from the one-sided differences and the full
-// difference d2 = a+ - a- (so no halving is needed: scaling by two is exact)
+// twice the limited slope of a cell (CW84 eq. 1.7-1.8) from its one-sided
+// differences dl, dr and the full difference d2 = a+ - a-: d2 limited to four
+// times either one-sided difference, zero at an extremum.  In FP32 it is
+// minmod(d2, minmod(4 dl, 4 dr)) with minmod(x, y) = median(x, y, 0) (the
+// smaller magnitude when x and y share a sign, else zero): two median-of-three
+// instructions, the same value as the general form (which FP64 keeps) up to
+// the sign of a zero.  Doubled, as the half of d2 would be rounded where it is
+// below the smallest normal number (the tails of a cold plasma in FP32), and
+// all variants have to agree there as well.
 template <typename C>
 __device__ __forceinline__ C limited_slope2(C dl, C dr, C d2)
 {
@@ -197,7 +186,8 @@ __device__ __forceinline__ C limited_slope2(C dl, C dr, C d2)
 
 // the face between a cell of average a0 and the next, d above it, with twice
 // their limited slopes s0 and s1 (CW84 eq. 1.6; the fused operations written
-// out, as a march's start and its iterations have to agree to the last bit)
+// out, as a march's start, its iterations and all variants have to agree to the
+// last bit)
 __device__ __forceinline__ float face_value(float a0, float d, float s1, float s0)
 {
     return fmaf(-(s1 - s0), (float)(0.5 / 6.0), fmaf(0.5f, d, a0));
@@ -251,9 +241,10 @@ __device__ __forceinline__ uint16_t narrow_bf16(double x, double &nv)
 //
 // The reconstruction is Colella & Woodward's, written in forms with fewer
 // operations that give the same values:
-//  * limited slope: copysign(max(0, min(|c|, 2 s dl, 2 s dr)), c) with
-//    c = (a+ - a-)/2 and s = sign(c) (zero unless dl and dr share a sign),
-//    in FP32 minmod(c, minmod(2 dl, 2 dr)) (limited_slope);
+//  * twice the limited slope: copysign(max(0, min(|c|, 4 s dl, 4 s dr)), c)
+//    with c = a+ - a- and s = sign(c) (zero unless dl and dr share a sign),
+//    in FP32 minmod(c, minmod(4 dl, 4 dr)) (limited_slope2), the faces'
+//    factor 1/6 halved;
 //  * monotonicity limiter on the face offsets dL = a - aL, dR = aR - a: the
 //    two overshoot corrections of the limiter are dL' = min(|dL|, 2|dR|) and
 //    dR' = min(|dR|, 2|dL|) (with the sign of the side), the extremum case is
@@ -321,10 +312,9 @@ __device__ __forceinline__ void march_unc(const Dev &D, const uint32_t *srow, ui
             q[u] = fetch(nxt[u]);
             // slope of cell t-1
             const C dl = a1 - a2, dr = a - a1;
-            const C cen = (C)0.5 * (a - a2);
-            const C da = limited_slope(dl, dr, cen);
+            const C da = limited_slope2(dl, dr, a - a2);
             // face between t-2 and t-1
-            const C face = a2 + (C)0.5 * (a1 - a2) - (da - da_prev) * (C)(1.0 / 6.0);
+            const C face = face_value(a2, a1 - a2, da, da_prev);
             // limited face offsets of cell t-2
             const C ai = a2;
             const C dL = ai - face_prev, dR = face - ai;
@@ -854,9 +844,8 @@ __device__ __forceinline__ void march_stream(const Dev &D, const uint32_t *X, co
             const C a = q[u];
             q[u] = fetch(src, fb + u);
             const C dl = a1 - a2, dr = a - a1;
-            const C cen = (C)0.5 * (a - a2);
-            const C da = limited_slope(dl, dr, cen);
-            const C face = a2 + (C)0.5 * dl - (da - da_prev) * (C)(1.0 / 6.0);
+            const C da = limited_slope2(dl, dr, a - a2);
+            const C face = face_value(a2, dl, da, da_prev);
             const C ai = a2;
             const C dL = ai - face_prev, dR = face - ai;
             const double dLp = (double)limited_offset(dL, dR), dRp = (double)limited_offset(dR, dL);
