@@ -63,3 +63,32 @@ def test_a_large_partition_takes_its_cells_in_several_launches():
     p.accelerate(dt, QM, EBd)
     q.accelerate(dt, QM, EBd)
     assert all(np.array_equal(x, y) for x, y in zip(p.export(), q.export()))
+
+
+@pytest.mark.parametrize("order", [(0, 1, 2), (2, 1, 0)])
+def test_a_value_that_is_not_a_number_spreads_as_in_the_oracle(order):
+    """A parabola next to a NaN is none: the same values are NaN as in the
+    oracle, not only those that take mass from the NaN's own velocity cell.
+    Spatial cells without one agree to 1e-12."""
+    n, nblk, dv = (3, 2, 3), (5, 4, 6), (2e4, 3e4, 2.5e4)
+    off, ids, f = random_state(n, nblk, 29, density=0.7, zero_frac=0.1)
+    f = f.copy()
+    poisoned = (0, 7, 11)
+    for c in poisoned:
+        f[64 * (off[c] + 11) + 21] = np.nan
+    w = W.Workload("random", n, (1e6, 1e6, 1e6), nblk, tuple(-2.0 * nblk[d] * dv[d] for d in range(3)), dv, 1.0, 1,
+                   0.0, 0, B.VL_F64, (0, 1, 2), off, ids, f)
+    rng = np.random.default_rng(7)
+    dt = 0.3 / (QM * 1e-8)
+    EB = np.concatenate([rng.normal(size=(w.ncell, 3)) * 1e-3, rng.normal(size=(w.ncell, 3)) * 0.6e-8], 1)
+    print_case("a NaN in three cells, order %s" % (order,))
+    p, o = B.Partition.from_workload(w), OraclePartition.from_workload(w)
+    p.accelerate(dt, QM, torch.tensor(EB.reshape(-1), dtype=torch.float64, device="cuda:0"), order=order)
+    o.accelerate(dt, QM, EB, order=order)
+    got, want = p.export(), o.export_local()
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    assert np.isnan(want[2]).sum() > len(poisoned)
+    assert np.array_equal(np.isnan(got[2]), np.isnan(want[2]))
+    for c in set(range(w.ncell)) - set(poisoned):
+        a, b = (s[2][64 * s[0][c]:64 * s[0][c + 1]] for s in (got, want))
+        assert np.max(np.abs(a - b)) <= 1e-12 * np.max(b)
