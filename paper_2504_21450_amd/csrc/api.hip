@@ -1169,72 +1169,39 @@ int vl_export_state(vl_partition *p, int64_t *cell_offsets, int32_t *block_ids, 
     const Dev &D = p->D;
     int rc = device_status(p);
     if (rc) return rc;
-    // bulk metadata copy; the lists are packed on the device
-    std::vector<int32_t> lcount((size_t)D.N), lsorted((size_t)D.N);
+    // the lists' lengths, then the lists packed on the device
+    std::vector<int32_t> lcount((size_t)D.N);
     VL_HIP(hipMemcpy(lcount.data(), D.lcount, (size_t)D.N * 4, hipMemcpyDeviceToHost));
-    VL_HIP(hipMemcpy(lsorted.data(), D.lsorted, (size_t)D.N * 4, hipMemcpyDeviceToHost));
     int64_t total = 0;
-    bool sorted = true;
     cell_offsets[0] = 0;
     for (int64_t q = 0; q < D.nlocal; q++) {
         const int x = (int)(q % D.n[0]), y = (int)((q / D.n[0]) % D.n[1]), z = (int)(q / ((int64_t)D.n[0] * D.n[1]));
-        const int64_t c = cell_index(D, x + H, y + H, z + H);
-        total += lcount[c];
-        sorted = sorted && lsorted[c] == lcount[c];
+        total += lcount[cell_index(D, x + H, y + H, z + H)];
         cell_offsets[q + 1] = total;
     }
     if (total > cap_blocks) return VL_ERR_ARG;
     if (total > 0 && !block_ids) return VL_ERR_ARG;
     if (total == 0) return VL_OK;
-    // Dead buffers hold the lists' offsets (per-cell sums), the packed slots
-    // (work items) and the packed ids, then the FP64 values (rows).  A partition
-    // has fewer blocks than row entries; the item array of a very large one may
-    // not hold every slot, and lists that are not in order (none after a step)
-    // are ordered on the host: then the slots make the round trip in pieces, as
-    // the values do.  (A step with the state of 7x5x3 sparse cells taken to the
-    // host: 7.4 ms with the whole list region copied and every cell's list
-    // sorted on the host, 6.5 ms so; the rest is the 53 MB of values.)
-    const int64_t item_i32 = (int64_t)(p->lay.item_cap * sizeof(Item)) / 4;
-    if (total > p->lay.row_cap) return VL_ERR_STATE;  // (not reached)
+    // Dead buffers hold the lists' offsets (per-cell sums), the packed ids, then
+    // the FP64 values (rows) and the packed slots (the list entry -> item array,
+    // which has room for every list).  A list is in ascending order here: given
+    // so at init, left so by every pruning, and only a step appends to it.  (A
+    // step with the state of 7x5x3 sparse cells taken to the host: 7.4 ms with
+    // the whole list region copied and every cell's list sorted on the host, 6.5
+    // ms so; the rest is the 53 MB of values.)
+    if (total > p->lay.row_cap) return VL_ERR_STATE;  // (not reached: a list entry has a slot)
     int64_t *doff = (int64_t *)D.cell_red;
-    int32_t *dslots = (int32_t *)D.items;
     double *dvals = (double *)D.rows;
-    const bool resident = sorted && total <= item_i32;
     VL_HIP(hipMemcpyAsync(doff, cell_offsets, (size_t)D.nlocal * 8, hipMemcpyHostToDevice, p->stream));
-    std::vector<int32_t> slots;
-    if (resident) {
-        launch_pack_lists(D, doff, D.rows, dslots, p->stream);
-        VL_HIP(hipGetLastError());
-        VL_HIP(hipMemcpyAsync(block_ids, D.rows, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
-        VL_HIP(hipStreamSynchronize(p->stream));
-    } else {
-        // (the list entry -> item array is dead here as well)
-        launch_pack_lists(D, doff, D.rows, D.litem, p->stream);
-        VL_HIP(hipGetLastError());
-        slots.resize((size_t)total);
-        VL_HIP(hipMemcpyAsync(block_ids, D.rows, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
-        VL_HIP(hipMemcpyAsync(slots.data(), D.litem, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
-        VL_HIP(hipStreamSynchronize(p->stream));
-        std::vector<std::pair<int32_t, int32_t>> ent;
-        for (int64_t q = 0; q < D.nlocal; q++) {
-            const int64_t b0 = cell_offsets[q], b1 = cell_offsets[q + 1];
-            ent.resize((size_t)(b1 - b0));
-            for (int64_t k = b0; k < b1; k++) ent[(size_t)(k - b0)] = {block_ids[k], slots[(size_t)k]};
-            std::sort(ent.begin(), ent.end());
-            for (int64_t k = b0; k < b1; k++) {
-                block_ids[k] = ent[(size_t)(k - b0)].first;
-                slots[(size_t)k] = ent[(size_t)(k - b0)].second;
-            }
-        }
-    }
-    const int64_t chunk = std::min<int64_t>((int64_t)(p->lay.row_cap * 4) / (BLK * 8), item_i32);
+    launch_pack_lists(D, doff, D.rows, D.litem, p->stream);
+    VL_HIP(hipGetLastError());
+    VL_HIP(hipMemcpyAsync(block_ids, D.rows, (size_t)total * 4, hipMemcpyDeviceToHost, p->stream));
+    VL_HIP(hipStreamSynchronize(p->stream));
+    const int64_t chunk = (int64_t)(p->lay.row_cap * 4) / (BLK * 8);
     if (chunk < 1) return VL_ERR_STATE;
     for (int64_t o = 0; o < total; o += chunk) {
         const int64_t m = std::min(chunk, total - o);
-        const int32_t *at = dslots + (resident ? o : 0);
-        if (!resident)
-            VL_HIP(hipMemcpyAsync(dslots, slots.data() + o, (size_t)m * 4, hipMemcpyHostToDevice, p->stream));
-        launch_gather(D, at, m, dvals, p->stream);
+        launch_gather(D, D.litem + o, m, dvals, p->stream);
         VL_HIP(hipGetLastError());
         VL_HIP(hipMemcpyAsync(f + o * BLK, dvals, (size_t)m * BLK * 8, hipMemcpyDeviceToHost, p->stream));
         VL_HIP(hipStreamSynchronize(p->stream));
