@@ -228,8 +228,11 @@ int vl_translate_step(vl_partition *p, double dt, int32_t mode, vl_step_stats *s
  * The call synchronises once to check the maps: if some cell's map cannot be
  * split (a step's own coefficient not positive, e.g. a rotation of half a
  * turn or more) it returns VL_ERR_SPLIT with f unchanged.  Velocity meshes of
- * more than 64 blocks along an axis are not supported (VL_ERR_ARG).  The
- * ghost domain is stale afterwards.
+ * more than 64 blocks along an axis are not supported (VL_ERR_ARG), nor those
+ * whose B blocks (B / 2 bytes), C columns of blocks across the largest face (8 C
+ * bytes) and longest axis of N blocks (384 (4 N + 1) bytes) come to more than
+ * 158 KiB in all (64 x 64 x 16 blocks do, 64 x 64 x 8 and 50 x 50 x 50 do not).
+ * The ghost domain is stale afterwards.
  * Errors: VL_ERR_ARG, VL_ERR_SPLIT, VL_ERR_CAPACITY (with stats), VL_ERR_STATE,
  * VL_ERR_HIP. */
 int vl_accelerate(vl_partition *p, double dt, double qm, const double *dev_fields, const int32_t *slice_order,
@@ -303,8 +306,11 @@ int vl_set_courant_override(vl_partition *p, const double *table, int32_t stride
 
 /* Diagnostics: copy the device book-keeping counters to out[0..n) (n <= 32):
  * [0] free-ring head, [1] free-ring tail, [2] free-ring limit, [3] ghost slots
- * used, [4] ghost list entries used, [5..6] local list entries used (regions
- * 0, 1), [7] work items, [8] work rows, [9] work counter, [10] error bits,
+ * used, [4] ghost list entries used (both as the last copied ghost update left
+ * them: a periodic partition that copies nothing does not change them, see
+ * vl_fill_ghosts), [5..6] local list entries used (regions 0, 1), [7] work
+ * items and [8] work rows of the last step's third shear (those it ran: of a
+ * partition that copies nothing, the local lines'), [9] always 0, [10] error bits,
  * [11..13] updated, [14..16] read phase-space cells, [17..19] items per shear
  * of the last step, [20] local list region in use, [21] updated and [22] read
  * phase-space cells summed over all shears since init (as in vl_step_stats:
@@ -347,7 +353,10 @@ int vl_autotune(vl_partition *p, double dt, int32_t mode, int32_t steps_per_vari
                 double *ms_out, int32_t ms_cap);
 
 /* Select one shear-kernel variant (0 .. number of variants - 1) for all
- * three shears.  VL_ERR_ARG outside that range. */
+ * three shears.  VL_ERR_ARG outside that range.  0 is what an untuned partition
+ * runs.  The numbers belong to one build of the library: a later one may have
+ * another kernel under the same number (0 and 7 have changed places), with the
+ * same results and another speed, so a stored choice is tuned again there. */
 int vl_set_variant(vl_partition *p, int32_t variant);
 
 /* Select the variant of each shear of the order (first, second, third);

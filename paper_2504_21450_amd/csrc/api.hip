@@ -811,7 +811,7 @@ int vl_accelerate(vl_partition *p, double dt, double qm, const double *dev_field
         const size_t lds = accel_lds_bytes(D, &ncols, &hc);
         VL_HIP(hipGetDevice(&dev));
         VL_HIP(hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-        if (lds == 0 || lds + 2048 > (size_t)maxlds) return VL_ERR_ARG;  // + the kernel's static LDS
+        if (lds == 0 || lds + 2048 > (size_t)maxlds) return VL_ERR_ARG;
     }
     double *maps = (double *)(p->ws + p->lay.accel);
     int *bad = (int *)(D.red + 64);

@@ -636,9 +636,11 @@ __global__ __launch_bounds__(64) void k_accel_remap(Dev D, AccelParams ap, int k
     }
 }
 
-// LDS bound of a velocity mesh (what a workgroup that held a cell's sets and a
-// whole block column would take; both kernels take less), or 0 if the mesh is
-// beyond the kernels' limits
+// The size by which a velocity mesh is accepted (see vl_accelerate), or 0 if an
+// axis is beyond ACC_MAX_NBLK blocks: a cell's block sets, with a block column's
+// averages and parabolas beside them.  Neither kernel holds both, so a mesh
+// within it fits them: the planner 12 bytes per 32 blocks and 12 per column
+// (77 KB at most), the remap 34 KB.
 size_t accel_lds_bytes(const Dev &D, int *ncols, int *hc)
 {
     int nc = 0, mx = 0;

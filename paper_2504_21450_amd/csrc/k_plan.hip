@@ -20,7 +20,8 @@
 //      look-up per old item), so the shear can take that line's residual.
 // The mask words of a block are registers of its thread: their number (NW, the
 // line's words rounded up to 1, 2, 4 or 8) is a template parameter, as eight for
-// every line spilled more scalars (8^3 dense cells: 23 -> 19 us a shear).
+// every line spilled more scalars (8^3 dense cells: 23 -> 19 us a shear; 95 to
+// 151 scalars are still kept in vector lanes, the fewer the shorter the line).
 // In a periodic partition (template parameter WR) only the local pencils are
 // planned: a pencil's ghost cells are its own first and last cells seen through
 // the period, so their presence bits are copied from those cells' bits, no list
@@ -137,7 +138,7 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_tmp[PNW];
     __shared__ long long s_ll[PNW];
-    __shared__ unsigned long long s_base[4];  // (unused), row, new-slot bases, status
+    __shared__ unsigned long long s_base[3];  // row and new-slot bases, status
     __shared__ long long s_ibp;               // the pencil's first item
     const int tid = threadIdx.x;
     const int L = pp.L, WL = pp.WL, W = D.W, R = pp.R;
@@ -207,9 +208,9 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
         }
     }
     for (int w = tid; w < W; w += PNT) s_bm[w] = 0u;
-    if (tid == 0) s_base[3] = failed(D) ? 1ull : 0ull;
+    if (tid == 0) s_base[2] = failed(D) ? 1ull : 0ull;
     __syncthreads();
-    if (s_base[3]) return;  // fail-stop, one decision per workgroup (nothing written yet)
+    if (s_base[2]) return;  // fail-stop, one decision per workgroup (nothing written yet)
     const int lane = tid & 63, wave = tid >> 6;
 
     // 1. union bitmap: a wavefront reads one cell's sorted list at a time,
@@ -520,14 +521,14 @@ __global__ __launch_bounds__(PNT) void k_plan(Dev D, PlanParams pp)
                 }
             }
             if (err) atomicOr(&D.ctl->err, err);
-            s_base[1] = rb;
-            s_base[2] = nb;
-            s_base[3] = ok;
+            s_base[0] = rb;
+            s_base[1] = nb;
+            s_base[2] = ok;
         }
         __syncthreads();
-        const unsigned long long rb = s_base[1], nb = s_base[2];
-        const bool rows_ok = (s_base[3] & 1) != 0;
-        const bool alloc_failed = (s_base[3] & 2) != 0;
+        const unsigned long long rb = s_base[0], nb = s_base[1];
+        const bool rows_ok = (s_base[2] & 1) != 0;
+        const bool alloc_failed = (s_base[2] & 2) != 0;
 
         // items and new blocks
         for (int k = tid; k < rn; k += PNT) {

@@ -106,14 +106,6 @@ constexpr int TABLE = WIN0 + 64 * NM + 72;
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 
-__device__ __forceinline__ double uniform_f64(double v)
-{
-    const uint64_t b = __double_as_longlong(v);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
 // a read-only array (or one whose element is read before this kernel writes
 // it) read at a wave-uniform place through the scalar cache
 template <typename T>
@@ -500,13 +492,26 @@ __device__ __forceinline__ void march_cond(const Dev &D, const uint32_t *srow, u
 struct VariantInfo {
     int style, pf, minw;
 };
-// The first is what an untuned partition runs: with the setup's registers out
-// of the marches it fits 64 VGPRs and eight waves per SIMD, and is the fastest
-// or within 2 % of it from 8^3 to 64x64x32 cells in every storage (ms per 1e9
-// cells read and written by the three shears, against the same code with eight
-// cells ahead and no occupancy asked: 16x16x8 FP64 1.98/2.03/2.61 : 2.26/2.31/
-// 3.04, 23x17x11 FP32 1.65/1.30/1.53 : 2.07/1.56/1.90, 64x64x32 FP64 1.97/1.96/
-// 2.06 : 1.96/1.92/2.19, 64x64x32 BF16 mixture 1.07/1.12/1.30 : 1.20/1.28/1.56).
+// The first is what an untuned partition runs.  Eight waves per SIMD leave it
+// 64 VGPRs, which BF16 on lines of up to 64 cells fits; the others spill a few
+// per item, outside the marches' loops (lines of up to 64 / 128 / 256 cells,
+// first shears and last: FP64 3, 3 / 3, 5 / 10, 14, FP32 2, 2 / 2, 4 / 4, 6,
+// BF16 0, 0 / 1, 3 / 3, 3).  ms per 1e9 cells read and written, the three shears
+// together, variants 0 : 8 : 7 : 1 : 3 (2 and 10 behind 7 everywhere but on 8^3
+// cells, where they lead 0 by 5 % and 3 %):
+//   16x16x8 sparse FP64     6.36 : 6.66 : 6.53 : 6.70 : 6.97
+//   64x64x32 sparse FP64    5.83 : 5.86 : 5.83 : 5.90 : 5.81
+//   16x128x16 sparse FP64   6.15 : 6.30 : 6.18 : 6.27 : 6.50
+//   8x250x8 sparse FP64     6.94 : 7.25 : 7.00 : 7.14 : 7.31
+//   23x17x11 sparse FP32    4.33 : 4.07 : 4.81 : 5.19 : 4.55
+//   40x40x20 mixture FP32   3.37 : 3.31 : 3.81 : 3.92 : 3.51
+//   8x250x8 sparse FP32     4.76 : 4.59 : 5.11 : 5.35 : 4.96
+//   24x24x12 mixture BF16   3.97 : 4.17 : 4.73 : 4.78 : 4.89
+//   64x64x32 mixture BF16   3.24 : 3.33 : 3.56 : 3.61 : 3.69
+//   128x128x8 mixture BF16  3.62 : 3.75 : 4.06 : 4.08 : 4.20
+//   8x250x8 sparse BF16     4.14 : 4.18 : 4.67 : 4.74 : 4.81
+// so beyond 8^3 cells it is the fastest or within 1 % of it in FP64 and BF16, and
+// up to 6 % behind variant 8 in FP32.
 constexpr VariantInfo VARIANTS[] = {{0, 4, 8}, {0, 8, 6}, {0, 4, 0}, {0, 16, 0}, {1, 8, 0}, {1, 8, 5},
                                    {2, 8, 0}, {0, 8, 0}, {0, 8, 8}, {2, 8, 8}, {0, 4, 6}};
 constexpr int NVARIANTS = sizeof(VARIANTS) / sizeof(VARIANTS[0]);
@@ -632,7 +637,7 @@ __device__ __forceinline__ void load_row(const Dev &D, const SweepParams &sp, co
 // ranks take a handful of instructions.  With eight 32-bit words for every
 // length and all reads at the item's start the setup was 2/5 of the vector
 // instructions of 24-cell BF16 lines (97 per updated cell, now 72), and the
-// registers it held allowed five waves per SIMD where eight fit now: step of
+// registers it held allowed five waves per SIMD where eight run now: step of
 // the 24x24x12 BF16 mixture 9.7 -> 7.7 ms, 16x16x8 FP64 2.80 -> 2.36 ms.
 template <int ST, bool LAST, int V, int NM>
 __device__ __forceinline__ void sweep_body(const Dev &D, const SweepParams &sp)

@@ -90,7 +90,7 @@ struct Ctl {
 };
 
 struct Item {
-    int32_t id;       // velocity block id
+    int32_t id;       // acceleration: packed block column (the shears do not read it: the block's id)
     int32_t key;      // shear: the block's coordinate along the axis; acceleration: local cell
     int64_t rowoff;   // first row entry
 };
