@@ -260,7 +260,9 @@ def run(p, w, storage, mode, steps, warmup, tune_steps, variant=None, graph_step
         "per_shear": [{"axis": "xyz"[w.order[s]],
                        "ms": prof["shear%d" % (s + 1)][0] / max(prof["shear%d" % (s + 1)][1], 1),
                        "algorithmic_gb": (c1["run_upd%d" % s] + c1["run_read%d" % s]) * bs / 1e9,
-                       "items": c1["items%d" % s]} for s in range(3)],
+                       # of the ghost scheme (a periodic partition runs fewer: a line's
+                       # images count there but are not sheared), unlike the bytes above
+                       "scheme_items": c1["items%d" % s]} for s in range(3)],
     }
     for s in out["per_shear"]:
         s["gbs"] = s["algorithmic_gb"] / (s["ms"] / 1e3) if s["ms"] > 0 else None

@@ -86,11 +86,10 @@ def test_moments_of_empty_and_single_block_cells():
 @pytest.mark.parametrize("storage", [B.VL_F64, B.VL_F32, B.VL_BF16])
 @pytest.mark.parametrize("nblk", [(20, 9, 11), (1, 40, 50)])
 def test_moments_of_scattered_and_compact_blocks(nblk, storage):
-    """The sums go by rows of blocks where 64 listed blocks hold runs of
-    consecutive ids and block by block where they are scattered: cells of
-    scattered blocks, of runs, and of both in turn, with lists that end within
-    and at a multiple of 64 blocks and in the second chunk of 1024, on a
-    velocity mesh with long rows and on one whose rows are single blocks.
+    """The sums go by rows of blocks on a velocity mesh with long rows and
+    block by block on one whose rows are single blocks: cells of scattered
+    blocks, of runs of consecutive ids, and of both in turn, with lists that end
+    within and at a multiple of 64 blocks and in the second chunk of 1024.
     Tolerances as in the file's other tests."""
     need_gpu()
     n, NB = (3, 3, 1), int(np.prod(nblk))
