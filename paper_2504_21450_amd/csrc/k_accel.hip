@@ -166,9 +166,8 @@ __device__ __forceinline__ double col_offset(double x, double y)
 // offsets dL = a - a_L, dR = a_R - a (CW84 eq. 1.6 faces) are formed from the
 // differences, limited, and put into eq. 1.5's profile, whose integral is
 //   x (a - dL + x (2 dL - dR - x (dL - dR))).
-// The limiter's minima and maxima pass over a NaN, so the offsets before it
-// enter once more, times zero: a parabola next to a NaN is none (the remaps of
-// 11x9x7 FP64 cells take 1.3 % longer for it, those of a BF16 mixture as long).
+// The limiter's minima and maxima pass over a NaN, so the neighbours'
+// difference enters once more, times zero: a parabola next to a NaN is none.
 __device__ __forceinline__ double col_head(double am2, double am, double a0, double ap, double ap2, double x)
 {
     constexpr double TWELFTH = 1.0 / 12.0;
@@ -177,7 +176,7 @@ __device__ __forceinline__ double col_head(double am2, double am, double a0, dou
     const double dm = col_slope2(h0, h1, a0 - am2), d0 = col_slope2(h1, h2, ap - am), dp = col_slope2(h2, h3, ap2 - a0);
     const double dL = fma(0.5, g1, (d0 - dm) * TWELFTH), dR = fma(0.5, g2, (d0 - dp) * TWELFTH);
     const double l = col_offset(dL, dR), r = col_offset(dR, dL);
-    return x * fma(x, fma(-x, l - r, fma(2.0, l, -r)), fma(0.0, dL, fma(0.0, dR, a0)) - l);
+    return x * fma(x, fma(-x, l - r, fma(2.0, l, -r)), fma(0.0, ap - am, a0) - l);
 }
 
 // shift sigma (cell units) of the velocity column at transverse velocity
