@@ -43,7 +43,7 @@
 // at a time with three barriers each: hot cells of a mixture (4,400 blocks
 // beside 80) ran long after the rest, and every cell's columns were a serial
 // chain.  Acceleration step with moments, before -> now: 24x24x12 BF16
-// mixture 19.2 -> 7.5 ms, 11x9x7 sparse FP64 1.49 -> 0.79 ms.
+// mixture 19.1 -> 6.2 ms, 11x9x7 sparse FP64 1.50 -> 0.66 ms.
 #include <algorithm>
 
 #include "vl_internal.h"
@@ -520,14 +520,18 @@ __device__ __forceinline__ double quad_next(double v, double wrap, bool first)
 // zero cells before and after, an odd multiple of 4
 __host__ __device__ inline int acc_stride(int mx) { return 4 * ((mx + 2) | 1); }
 
-// Bound by FP64 vector instructions: 1.1 to 1.9 ms a remap of the 3.5 million
-// blocks of a 24x24x12 BF16 mixture (its bytes, read and written once, take
-// 0.2 ms), of which 1.5 to 2.4 ms went to 171 vector instructions a block
-// before a face's five cells lay at one address with offsets and the parabola
-// was put in face offsets (fewer roundings, too: the error against 64 bits on
-// 11x9x7 FP64 cells went from 5.0e-15 to 4.6e-15).  A workgroup is one
-// wavefront, so the columns in LDS, 16 acc_stride values of the storage type
-// each, pack a compute unit's 160 KiB without a remainder.
+// In BF16 bound by vector instructions: a remap of the 6.0 million blocks,
+// created ones included, of a 24x24x12 mixture takes 1.5 ms at 118 instructions
+// a block, 75 % of the issue slots (its bytes, read and written once, take 0.35
+// ms).  It was 171 instructions, and a step 8.8 instead of 7.5 ms, before a
+// face's five cells lay at one address with offsets and the parabola was put in
+// face offsets (fewer roundings, too: the error against 64 bits on 11x9x7 FP64
+// cells went from 5.0e-15 to 4.6e-15).  In FP64 it is bound by latency: 47 % of
+// the issue slots and 2.3 TB/s on 11x9x7 sparse cells (0.12 ms for 0.29 million
+// blocks), as a column of a mesh 25 blocks long takes 13.8 KB of LDS and a
+// compute unit so holds 11 wavefronts.  A workgroup is one wavefront, so the
+// columns in LDS, 16 acc_stride values of the storage type each, pack a compute
+// unit's 160 KiB without a remainder.
 template <int ST>
 __global__ __launch_bounds__(64) void k_accel_remap(Dev D, AccelParams ap, int k)
 {

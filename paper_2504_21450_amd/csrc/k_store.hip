@@ -349,10 +349,11 @@ void launch_cell_counts(const Dev &D, hipStream_t st)
 // axis (uniform over the block, from the two blocks' packed coordinates; the
 // units are applied to the sums at the end), the lanes add f, f kx and f kx^2
 // per block, and when the sorted list goes on to another row of blocks (ky or
-// kz changes) the row's three sums enter the ten sums of f, f k, f k k^T: the
-// kernel is bound by FP64 vector instructions, and these are 9 a block and 10
-// a row (4 to 25 blocks) instead of 18 a block: 1.84 -> 1.41 ms for the 28
-// million BF16 blocks of a 48x48x24 mixture (0.75 ms at the rate of a copy).
+// kz changes) the row's three sums enter the ten sums of f, f k, f k k^T: 9
+// FP64 instructions a block and 10 a row (4 to 25 blocks) instead of 18 a block,
+// 1.84 -> 1.41 ms for the 28 million BF16 blocks of a 48x48x24 mixture (0.75 ms
+// at the rate of a copy; 43 % of the issue slots and 2.7 TB/s of 128-byte
+// blocks, neither at its limit; FP64 blocks come at 5.6 TB/s).
 // On a mesh of one or two blocks along x nearly every block ends a row, which
 // costs more than the 18, so there each block enters the ten sums by itself
 // (template parameter ROWS; 300 blocks in each of 32x32x16 cells on a mesh of
