@@ -361,7 +361,7 @@ void launch_cell_counts(const Dev &D, hipStream_t st)
 // meshes, which neither sampling nor pruning leaves, are summed by rows as
 // well: choosing by the ids of the list made them 6 % faster and every other
 // list 2 to 8 % slower (registers and one more test per 64 blocks).
-// each lane's offset o within the block enters once at the end:
+// Each lane's offset o within the block enters once at the end:
 //   sum f (c + o) = S1c + o S0,  sum f (c+o)(c+o)^T = S2c + S1c o^T + o S1c^T + S0 o o^T.
 // ---------------------------------------------------------------------------
 // packed block coordinates bx | by << 10 | bz << 20
